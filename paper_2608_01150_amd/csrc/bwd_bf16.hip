@@ -653,6 +653,24 @@ __global__ __launch_bounds__(kDqThreads, 1) void bwd_dq_kernel(BwdParams p) {
 
 }  // namespace
 
+template <int D>
+hipError_t launch_dkdv(BwdParams p, hipStream_t s) {
+  const int grid = launch_grid(reinterpret_cast<const void*>(bwd_dkdv_kernel<D>), kDkdvThreads, p.n_kv_items, p.wq_kv);
+  if (grid < 0) return hipErrorInvalidValue;
+  if (grid == p.n_kv_items) p.wq_kv = nullptr;  // a single round: nothing to claim
+  hipLaunchKernelGGL(bwd_dkdv_kernel<D>, dim3(grid), dim3(kDkdvThreads), 0, s, p);
+  return hipGetLastError();
+}
+
+template <int D>
+hipError_t launch_dq(BwdParams p, hipStream_t s) {
+  const int grid = launch_grid(reinterpret_cast<const void*>(bwd_dq_kernel<D>), kDqThreads, p.n_q_items, p.wq_q);
+  if (grid < 0) return hipErrorInvalidValue;
+  if (grid == p.n_q_items) p.wq_q = nullptr;  // a single round: nothing to claim
+  hipLaunchKernelGGL(bwd_dq_kernel<D>, dim3(grid), dim3(kDqThreads), 0, s, p);
+  return hipGetLastError();
+}
+
 hipError_t launch_bwd_bf16(const BwdParams& p, int head_dim, int stage, hipStream_t s) {
   const dim3 block(NT);
   if (stage == 0) {
@@ -664,20 +682,10 @@ hipError_t launch_bwd_bf16(const BwdParams& p, int head_dim, int stage, hipStrea
     else hipLaunchKernelGGL(bwd_pre_kernel<64>, grid, block, 0, s, p);
   } else if (stage == 1) {
     if (p.n_kv_items == 0) return hipSuccess;
-    const void* kern = head_dim == 128 ? reinterpret_cast<const void*>(bwd_dkdv_kernel<128>)
-                                       : reinterpret_cast<const void*>(bwd_dkdv_kernel<64>);
-    const int grid = launch_grid(kern, kDkdvThreads, p.n_kv_items, p.wq_kv);
-    if (grid < 0) return hipErrorInvalidValue;
-    if (head_dim == 128) hipLaunchKernelGGL(bwd_dkdv_kernel<128>, dim3(grid), dim3(kDkdvThreads), 0, s, p);
-    else hipLaunchKernelGGL(bwd_dkdv_kernel<64>, dim3(grid), dim3(kDkdvThreads), 0, s, p);
+    return head_dim == 128 ? launch_dkdv<128>(p, s) : launch_dkdv<64>(p, s);
   } else {
     if (p.n_q_items == 0) return hipSuccess;
-    const void* kern = head_dim == 128 ? reinterpret_cast<const void*>(bwd_dq_kernel<128>)
-                                       : reinterpret_cast<const void*>(bwd_dq_kernel<64>);
-    const int grid = launch_grid(kern, kDqThreads, p.n_q_items, p.wq_q);
-    if (grid < 0) return hipErrorInvalidValue;
-    if (head_dim == 128) hipLaunchKernelGGL(bwd_dq_kernel<128>, dim3(grid), dim3(kDqThreads), 0, s, p);
-    else hipLaunchKernelGGL(bwd_dq_kernel<64>, dim3(grid), dim3(kDqThreads), 0, s, p);
+    return head_dim == 128 ? launch_dq<128>(p, s) : launch_dq<64>(p, s);
   }
   return hipGetLastError();
 }

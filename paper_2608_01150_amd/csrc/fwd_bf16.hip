@@ -435,16 +435,17 @@ __global__ __launch_bounds__(NT, 1) void fwd_bf16_kernel(FwdParams p) {
 
 }  // namespace
 
-hipError_t launch_fwd_bf16(const FwdParams& p, int head_dim, hipStream_t s) {
-  const void* kern = head_dim == 128 ? reinterpret_cast<const void*>(fwd_bf16_kernel<128>)
-                                     : reinterpret_cast<const void*>(fwd_bf16_kernel<64>);
-  const int grid = launch_grid(kern, NT, p.n_items, p.wq);
+template <int D>
+hipError_t launch_d(FwdParams p, hipStream_t s) {
+  const int grid = launch_grid(reinterpret_cast<const void*>(fwd_bf16_kernel<D>), NT, p.n_items, p.wq);
   if (grid < 0) return hipErrorInvalidValue;
-  if (head_dim == 128)
-    hipLaunchKernelGGL(fwd_bf16_kernel<128>, dim3(grid), dim3(NT), 0, s, p);
-  else
-    hipLaunchKernelGGL(fwd_bf16_kernel<64>, dim3(grid), dim3(NT), 0, s, p);
+  if (grid == p.n_items) p.wq = nullptr;  // a single round: nothing to claim
+  hipLaunchKernelGGL(fwd_bf16_kernel<D>, dim3(grid), dim3(NT), 0, s, p);
   return hipGetLastError();
+}
+
+hipError_t launch_fwd_bf16(const FwdParams& p, int head_dim, hipStream_t s) {
+  return head_dim == 128 ? launch_d<128>(p, s) : launch_d<64>(p, s);
 }
 
 }  // namespace zl

@@ -252,7 +252,7 @@ __device__ __forceinline__ float xor32_sum(float v) {
 // (grid G <= n) first runs position b, i.e. the first round of a
 // one-item-per-workgroup launch; afterwards it claims further positions of
 // its own XCD's queue with a device-scope atomic counter, and once that queue
-// is empty those of the other XCDs' queues in turn.  The XCDs of one GPU run
+// is empty those of the next XCD's queue that holds any.  The XCDs of one GPU run
 // at different speeds (several percent apart under load), and a fixed share
 // of the items per XCD leaves the fast ones idle while the slowest finishes;
 // here an XCD that runs ahead takes over the tail of the others' queues.
@@ -272,25 +272,43 @@ __device__ __forceinline__ int xcd_id() {
 __device__ __forceinline__ int wq_claim(int* ctr, int tries) { return atomicAdd(&ctr[(xcd_id() + tries) & 7], 1); }
 
 // Work-table index of this workgroup's next item, or -1 when every queue is
-// empty.  *tries (workgroup state, in LDS) counts the queues found empty;
-// pending is a claim from wq_claim on the current queue, or -1.
+// empty.  *tries (workgroup state, in LDS) is the queue in use as an offset from
+// the workgroup's XCD (8: all empty); pending is a claim from wq_claim on that
+// queue, or -1.  When the claim finds its queue empty, one look at all eight
+// counters picks the next queue that still holds items: claiming from each in
+// turn made every workgroup wait for up to eight atomics one after another when
+// it ran out of work (3 to 12 us at the end of a launch; two round trips now).
+// A queue whose claim fails stays empty, so the loop ends after at most nine
+// looks.
 __device__ __forceinline__ int wq_next(int* ctr, int n, int chunk, int* tries, int pending) {
   int t = *tries;
+  if (t >= 8) return -1;
   const int grid = (int)gridDim.x;
-  while (t < 8) {
-    const int y = (xcd_id() + t) & 7;
-    const int len = (n - y + 7) >> 3;      // positions y + 8k below n
-    const int first = (grid - y + 7) >> 3;  // of those, taken by the first round
-    const int k = first + (pending >= 0 ? pending : atomicAdd(&ctr[y], 1));
-    pending = -1;
-    if (k < len) {
-      *tries = t;
-      return dispatch_item(8 * k + y, n, chunk);
+  const int xcd = xcd_id();
+  auto len = [&](int y) { return (n - y + 7) >> 3; };        // positions y + 8k below n
+  auto first = [&](int y) { return (grid - y + 7) >> 3; };   // of those, taken by the first round
+  for (;;) {
+    if (pending >= 0) {
+      const int y = (xcd + t) & 7, k = first(y) + pending;
+      if (k < len(y)) {
+        *tries = t;
+        return dispatch_item(8 * k + y, n, chunk);
+      }
     }
-    ++t;
+    int c[8];
+#pragma unroll
+    for (int i = 0; i < 8; ++i) c[i] = __hip_atomic_load(&ctr[i], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    int mask = 0;  // bit y: queue y still holds items
+#pragma unroll
+    for (int y = 0; y < 8; ++y) mask |= (first(y) + c[y] < len(y) ? 1 : 0) << y;
+    mask = (mask | mask << 8) >> xcd;  // bit i: queue (xcd + i) % 8
+    if ((mask & 0xFF) == 0) {
+      *tries = 8;
+      return -1;
+    }
+    t = __ffs(mask) - 1;
+    pending = wq_claim(ctr, t);
   }
-  *tries = t;
-  return -1;
 }
 
 // Called once per workgroup after its last item.
