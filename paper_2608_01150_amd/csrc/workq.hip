@@ -64,6 +64,14 @@ zl_status stream_counters(hipStream_t s, int** out) {
   return ZL_OK;
 }
 
+int device_cus() {
+  int dev = 0, n = 0;
+  if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= kMaxDevices) return 256;
+  DeviceState& d = g_dev[dev];
+  if (d.cus == 0 && hipDeviceGetAttribute(&n, hipDeviceAttributeMultiprocessorCount, dev) == hipSuccess) d.cus = n;
+  return d.cus > 0 ? d.cus : 256;
+}
+
 int launch_grid(const void* kernel, int block, int n_items, const int* ctr) {
   if (!ctr) return n_items;
   int dev = 0;

@@ -247,6 +247,29 @@ std::vector<zl::Item> build_items(const zl_seg_desc* d, int32_t H, int op, TileC
   return items;
 }
 
+// How far the query tiles of a bf16 forward or dQ launch are split: 0 runs its
+// items as they are (256 rows), 1 and 2 as halves and quarters (see KeySplit in
+// zl_device.h), each done in about 0.6 and 0.45 of a full tile's time per key
+// (6,100 / 3,620 / 2,740 cycles per 128 keys in the forward).  So they pay where
+// a launch leaves compute units idle and all of the smaller tiles still run in
+// one round; with more rounds the halves' higher total costs as much as a better
+// filled last round gives (one segment, 12 heads, forward and backward, 2 rounds
+// of full tiles against 3 of halves: 5,461 tokens +1%, 6,400 -6%, 8,160 -1.7%;
+// 3 x 1560 tokens, 1 round against 2: +17%).  Measured: one 1560-token image, 12
+// heads, 84 items, as halves: forward 44.7 -> 33.0 us, dQ 54.6 -> 39.1 us; one
+// 448-token image as quarters: forward 16.4 -> 13.0 us.  Only the items' rows
+// count, so a shard's ring step splits as the backward of all its blocks does.
+int choose_split(const std::vector<zl::Item>& items, int tile_m) {
+  const size_t slots = (size_t)zl::device_cus();
+  for (int split = 2; split > 0 && items.size() <= slots; --split) {
+    const int m = tile_m >> split;
+    size_t n = 0;
+    for (const zl::Item& it : items) n += (size_t)((it.q_len + m - 1) / m);
+    if (n <= slots) return split;
+  }
+  return 0;
+}
+
 struct MergeTable {
   std::vector<zl::MergeSeg> segs;
   std::vector<int32_t> slots;
@@ -275,6 +298,7 @@ struct Plan {
   std::vector<char> host;       // host copy (source of the upload)
   int32_t n_items = 0;          // forward items, or backward dK/dV items
   int32_t n_items2 = 0;         // backward dQ items
+  int32_t split = 0;            // choose_split of the forward or dQ items (bf16)
   int32_t n_segs = 0;
   int64_t n_units = 0;
   size_t slots_offset = 0;      // merge: slot list; backward: dQ items
@@ -339,6 +363,7 @@ zl_status build_plan_host(const zl_seg_desc* d, int32_t H, zl_dtype dt, int op, 
       return fail(ZL_ERR_UNSUPPORTED, "too many work items");
     p.n_items = (int32_t)kv.size();
     p.n_items2 = (int32_t)qi.size();
+    p.split = choose_split(qi, zl::kDqTileM);
     p.slots_offset = align256(kv.size() * sizeof(zl::Item));
     p.host.assign(p.slots_offset + qi.size() * sizeof(zl::Item), 0);
     if (!kv.empty()) std::memcpy(p.host.data(), kv.data(), kv.size() * sizeof(zl::Item));
@@ -349,6 +374,7 @@ zl_status build_plan_host(const zl_seg_desc* d, int32_t H, zl_dtype dt, int op, 
     std::vector<zl::Item> items = build_items(d, H, base_op, tile_cfg(dt, base_op), step);
     if (items.size() > (size_t)INT32_MAX) return fail(ZL_ERR_UNSUPPORTED, "too many work items");
     p.n_items = (int32_t)items.size();
+    if (dt == ZL_BF16) p.split = choose_split(items, zl::kFwdTileM);
     p.host.resize(items.size() * sizeof(zl::Item));
     if (!items.empty()) std::memcpy(p.host.data(), items.data(), p.host.size());
   }
@@ -603,7 +629,8 @@ zl_status zl_attn_fwd_ex(const zl_seg_desc* desc, int32_t H, int32_t hd, zl_dtyp
   p.part_bf16 = part_dt == ZL_BF16 ? 1 : 0;
   p.lse_part = lse_part;
   p.items = static_cast<const zl::Item*>(plan->dev);
-  p.n_items = plan->n_items;
+  p.split = plan->split;
+  p.n_items = plan->n_items << p.split;
   p.num_heads = H;
   p.slot_stride = (int64_t)sh.total_q * H * hd;
   p.lse_slot_stride = (int64_t)sh.total_q * H;
@@ -649,7 +676,8 @@ zl_status zl_attn_fwd_step(const zl_seg_desc* desc, int32_t H, int32_t hd, zl_dt
   p.out = out;
   p.lse = lse;
   p.items = static_cast<const zl::Item*>(plan->dev);
-  p.n_items = plan->n_items;
+  p.split = plan->split;
+  p.n_items = plan->n_items << p.split;
   p.num_heads = H;
   p.scale = scale;
   p.scale_log2 = scale * 1.4426950408889634f;
@@ -846,11 +874,11 @@ zl_status validate_bwd(const BwdCall& c, Shape* sh) {
 
 
 // Enqueues the three backward kernels.  tables: the dK/dV items, then (at
-// q_offset bytes) the dQ items; workspace: bwd_workspace_bytes of device
+// q_offset bytes) the dQ items, split by split_q; workspace: bwd_workspace_bytes of device
 // memory.  No early return for Tq = 0: the ranges of a SHARD without query
 // rows still get their (zero) dK/dV.
 zl_status launch_bwd(const BwdCall& c, const Shape& sh, const void* tables, size_t q_offset, int32_t n_kv,
-                     int32_t n_q, void* workspace, hipStream_t s) {
+                     int32_t n_q, int32_t split_q, void* workspace, hipStream_t s) {
   const bool first = !c.step || (c.flags & ZL_STEP_FIRST), last = !c.step || (c.flags & ZL_STEP_LAST);
   zl::BwdParams p{};
   p.q = c.q;
@@ -868,7 +896,8 @@ zl_status launch_bwd(const BwdCall& c, const Shape& sh, const void* tables, size
   p.kv_items = reinterpret_cast<const zl::Item*>(base);
   p.n_kv_items = n_kv;
   p.q_items = reinterpret_cast<const zl::Item*>(base + q_offset);
-  p.n_q_items = n_q;
+  p.split_q = split_q;
+  p.n_q_items = n_q << p.split_q;
   p.num_heads = c.H;
   p.total_q = sh.total_q;
   p.scale = c.scale;
@@ -903,7 +932,7 @@ zl_status attn_bwd_impl(const BwdCall& c, void* workspace, size_t ws_bytes, void
   Plan* plan = nullptr;
   hipStream_t s = static_cast<hipStream_t>(stream);
   if ((st = get_plan(c.desc, c.H, c.hd, c.dt, c.step ? kPlanBwdStep : ZL_OP_BWD, s, &plan)) != ZL_OK) return st;
-  return launch_bwd(c, sh, plan->dev, plan->slots_offset, plan->n_items, plan->n_items2, workspace, s);
+  return launch_bwd(c, sh, plan->dev, plan->slots_offset, plan->n_items, plan->n_items2, plan->split, workspace, s);
 }
 
 }  // namespace
@@ -932,7 +961,8 @@ zl_status attn_bwd_scratch(const zl_seg_desc* desc, int32_t H, int32_t hd, zl_dt
   if (!hp->host.empty() &&
       hipMemcpyAsync(base, hp->host.data(), hp->host.size(), hipMemcpyHostToDevice, s) != hipSuccess)
     return fail(ZL_ERR_HIP, "copy of the work tables into the scratch failed");
-  return launch_bwd(c, sh, base, hp->slots_offset, hp->n_items, hp->n_items2, static_cast<char*>(base) + tables, s);
+  return launch_bwd(c, sh, base, hp->slots_offset, hp->n_items, hp->n_items2, hp->split,
+                    static_cast<char*>(base) + tables, s);
 }
 
 }  // namespace zl

@@ -65,6 +65,7 @@ struct FwdParams {
   float scale;           // softmax scale
   float scale_log2;      // softmax scale * log2(e)
   int32_t xcd_chunk;
+  int32_t split;         // the launch runs n_items = (table items) << split sub-items (see sub_item)
   // Ring-step mode (zl_attn_fwd_step): SHARD items fold their block into the
   // running (o_acc, lse_acc) instead of writing a partial slot.
   int32_t step_mode;
@@ -112,7 +113,8 @@ struct BwdParams {
   const Item* kv_items;        // dK/dV items: one key tile against all of its segment's queries
   int32_t n_kv_items;
   const Item* q_items;         // dQ items: one query tile against every key of its segment
-  int32_t n_q_items;
+  int32_t n_q_items;           // sub-items: (table items) << split_q
+  int32_t split_q;
   int32_t num_heads;
   int64_t total_q;             // Tq
   float scale;
@@ -143,6 +145,9 @@ zl_status stream_counters(hipStream_t s, int** out);
 // work queues: n_items when ctr is NULL, else min(n_items, resident
 // workgroups of the device).
 int launch_grid(const void* kernel, int block, int n_items, const int* ctr);
+
+// Compute units of the current device (256, the MI355X's, where none is usable).
+int device_cus();
 
 hipError_t launch_fwd_bf16(const FwdParams& p, int head_dim, hipStream_t s);
 hipError_t launch_fwd_fp32(const FwdParams& p, int head_dim, hipStream_t s);

@@ -1,0 +1,58 @@
+"""Query tiles of 256, 128 and 64 rows (forward and dQ) at their edges against
+the fp64 oracle.  The library picks the tile by the launch's size: few heads
+give tiles of 64 rows (four waves share a row group), tens of heads 128, and
+hundreds of items whole tiles of 256; the oracle's result is the same.
+Bounds as in the other parity tests."""
+import pytest
+import torch
+
+from tests import _descs
+from tests._gpu import HAVE_GPU
+from tests.test_gpu_parity import run_and_compare
+
+pytestmark = [pytest.mark.gpu, pytest.mark.skipif(not HAVE_GPU, reason="needs a GPU")]
+
+WHOLE = (1, 31, 33, 64, 65, 127, 128, 129, 255, 257)   # rows = keys: tile, row-group and step edges
+
+
+@pytest.mark.parametrize("hd", [64, 128])
+@pytest.mark.parametrize("heads", [1, 9, 40])
+def test_tile_edges(heads, hd):
+    # the whole segments, then a shard of 130 rows against blocks of 32, 0, 97 and 385 keys
+    blocks = (32, 0, 97, 385)
+    cu_q, cu_k = [0], [0]
+    for n in WHOLE:
+        cu_q.append(cu_q[-1] + n)
+        cu_k.append(cu_k[-1] + n)
+    cu_q.append(cu_q[-1] + 130)
+    for n in blocks:
+        cu_k.append(cu_k[-1] + n)
+    w = len(WHOLE)
+    d = _descs.desc(cu_q=cu_q, kind=(0,) * w + (1,), kv_first=tuple(range(w + 1)), kv_count=(1,) * w + (len(blocks),),
+                    cu_k=cu_k, block_index=(0,) * w + tuple(range(len(blocks))), num_slots=len(blocks))
+    run_and_compare(d, heads, hd, torch.bfloat16, 60 + heads + hd)
+
+
+@pytest.mark.parametrize("heads", [2, 20, 160])
+def test_one_long_segment(heads):
+    # one segment: 3 tiles of 256 rows, the last one ragged; several 128-key tiles
+    d = _descs.desc(cu_q=(0, 523), kind=(0,), kv_first=(0,), kv_count=(1,), cu_k=(0, 523), block_index=(0,), num_slots=0)
+    run_and_compare(d, heads, 128, torch.bfloat16, 70 + heads)
+
+
+def test_scores_jump_across_parts():
+    """Keys that beat the running maximum far beyond the fast path's bound, each time in another wave's
+    share of the keys: the parts are combined at different maxima."""
+    from tests._gpu import api, to64
+    import numpy as np
+    import oracle
+    n, hd = 300, 128
+    g = torch.Generator().manual_seed(81)
+    q, k, v = (torch.randn((n, 1, hd), generator=g).to(torch.bfloat16) for _ in range(3))
+    for i, f in ((10, 8), (40, 16), (75, 32), (110, 64), (200, 96), (290, 128)):
+        k[i] *= f
+    d = _descs.desc(cu_q=(0, n), kind=(0,), kv_first=(0,), kv_count=(1,), cu_k=(0, n), block_index=(0,), num_slots=0)
+    out, lse, _, _ = api.attn_fwd(api.SegDesc.of(d), q.cuda(), k.cuda(), v.cuda(), hd ** -0.5)
+    ref = oracle.packed_forward(d, *(t.double().numpy() for t in (q, k, v)), hd ** -0.5)
+    assert np.abs(to64(out) - ref["out"]).max() <= 2e-2
+    assert np.abs(to64(lse) - ref["lse"]).max() <= 1e-3
