@@ -5,10 +5,12 @@
 // consecutive lanes own a unit, each holding 4 or 8 consecutive values of the
 // row, so every slot's partial row is read with one fully coalesced 16-byte
 // load per lane.  Slots are taken
-// in passes of 8 whose loads are all issued before any is used, combined
+// in passes of PASS slots whose loads are all issued before any is used, combined
 // online across passes (running maximum and sum).  The kernel is HBM-bound:
 // per unit it reads S*(4d+4) bytes (S*(2d+4) with bf16 partials, one 8-byte
-// load per lane and slot) and writes 2d+4 (bf16) or 4d+4 bytes.
+// load per lane and slot) and writes 2d+4 (bf16) or 4d+4 bytes; the bf16 output
+// is stored non-temporally (8 fp32 slots of 9,450 rows, 40 heads: 284 -> 271 us,
+// 6.1 TB/s).
 
 #include "zl_device.h"
 #include "zl_internal.h"
@@ -17,9 +19,7 @@ namespace zl {
 namespace {
 
 constexpr int NT = 256;
-constexpr int kSlotsPerPass = 8;
-
-template <int D, bool OUT_BF16, bool PART_BF16>
+template <int D, bool OUT_BF16, bool PART_BF16, int PASS>
 __global__ __launch_bounds__(NT) void merge_kernel(MergeParams p) {
   // A lane holds E consecutive values of the row: 4 fp32 or 8 bf16 partial
   // values, so each slot is read with one 16-byte load per lane either way.
@@ -47,12 +47,12 @@ __global__ __launch_bounds__(NT) void merge_kernel(MergeParams p) {
   float acc[E];
 #pragma unroll
   for (int t = 0; t < E; ++t) acc[t] = 0.f;
-  for (int b0 = 0; b0 < sg.slot_count; b0 += kSlotsPerPass) {
-    const int nb = min(kSlotsPerPass, sg.slot_count - b0);
-    float lb[kSlotsPerPass];
-    u32x4 ob[kSlotsPerPass];
+  for (int b0 = 0; b0 < sg.slot_count; b0 += PASS) {
+    const int nb = min(PASS, sg.slot_count - b0);
+    float lb[PASS];
+    u32x4 ob[PASS];
 #pragma unroll
-    for (int b = 0; b < kSlotsPerPass; ++b) {
+    for (int b = 0; b < PASS; ++b) {
       lb[b] = -INFINITY;
       ob[b] = u32x4{0u, 0u, 0u, 0u};
       if (b < nb) {
@@ -64,7 +64,7 @@ __global__ __launch_bounds__(NT) void merge_kernel(MergeParams p) {
     }
     float mb = lb[0];
 #pragma unroll
-    for (int b = 1; b < kSlotsPerPass; ++b) mb = fmaxf(mb, lb[b]);
+    for (int b = 1; b < PASS; ++b) mb = fmaxf(mb, lb[b]);
     if (mb == -INFINITY) continue;  // every slot of this pass is empty
     const float mn = fmaxf(m, mb);
     const float r = expf(m - mn);   // 0 while m is still -inf
@@ -72,7 +72,7 @@ __global__ __launch_bounds__(NT) void merge_kernel(MergeParams p) {
 #pragma unroll
     for (int t = 0; t < E; ++t) acc[t] *= r;
 #pragma unroll
-    for (int b = 0; b < kSlotsPerPass; ++b) {
+    for (int b = 0; b < PASS; ++b) {
       const float w = expf(lb[b] - mn);  // 0 for empty slots
       l += w;
 #pragma unroll
@@ -93,8 +93,8 @@ __global__ __launch_bounds__(NT) void merge_kernel(MergeParams p) {
 #pragma unroll
     for (int t = 0; t < E / 2; ++t) wv[t] = pack_bf16(acc[2 * t], acc[2 * t + 1]);
     uint16_t* dst = static_cast<uint16_t*>(p.out) + row * D + sub * E;
-    if constexpr (E == 8) *reinterpret_cast<u32x4*>(dst) = u32x4{wv[0], wv[1], wv[2], wv[3]};
-    else *reinterpret_cast<u32x2*>(dst) = u32x2{wv[0], wv[1]};
+    if constexpr (E == 8) __builtin_nontemporal_store(u32x4{wv[0], wv[1], wv[2], wv[3]}, reinterpret_cast<u32x4*>(dst));
+    else __builtin_nontemporal_store(u32x2{wv[0], wv[1]}, reinterpret_cast<u32x2*>(dst));
   } else {
     float* dst = static_cast<float*>(p.out) + row * D + sub * E;
 #pragma unroll
@@ -105,10 +105,23 @@ __global__ __launch_bounds__(NT) void merge_kernel(MergeParams p) {
 
 }  // namespace
 
+// Slots per pass: 8 where one pass then holds every slot (fp32, 8 slots, 9,450
+// rows of 40 heads: 267 us, 4 per pass 268), and for more fp32 slots (16 slots:
+// 129.4 against 129.8).  Otherwise 4, whose fewer registers leave more waves in
+// flight: 3 fp32 slots 17.5 -> 16.8 us, 16 bf16 slots 128.8 -> 111.4 us (8 bf16
+// slots 18.2 with 8 per pass, 18.6 with 4).
+template <int D, bool OUT_BF16, bool PART_BF16>
+void launch_merge_p(const MergeParams& p, dim3 grid, dim3 block, hipStream_t s) {
+  if (p.max_slots <= 4 || (PART_BF16 && p.max_slots > 8))
+    hipLaunchKernelGGL((merge_kernel<D, OUT_BF16, PART_BF16, 4>), grid, block, 0, s, p);
+  else
+    hipLaunchKernelGGL((merge_kernel<D, OUT_BF16, PART_BF16, 8>), grid, block, 0, s, p);
+}
+
 template <int D, bool OUT_BF16>
 void launch_merge_d(const MergeParams& p, bool part_bf16, dim3 grid, dim3 block, hipStream_t s) {
-  if (part_bf16) hipLaunchKernelGGL((merge_kernel<D, OUT_BF16, true>), grid, block, 0, s, p);
-  else hipLaunchKernelGGL((merge_kernel<D, OUT_BF16, false>), grid, block, 0, s, p);
+  if (part_bf16) launch_merge_p<D, OUT_BF16, true>(p, grid, block, s);
+  else launch_merge_p<D, OUT_BF16, false>(p, grid, block, s);
 }
 
 hipError_t launch_merge(const MergeParams& p, int head_dim, bool out_bf16, bool part_bf16, hipStream_t s) {

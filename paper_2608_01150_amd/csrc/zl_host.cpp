@@ -300,6 +300,7 @@ struct Plan {
   int32_t n_items2 = 0;         // backward dQ items
   int32_t split = 0;            // choose_split of the forward or dQ items (bf16)
   int32_t n_segs = 0;
+  int32_t max_slots = 0;        // merge: largest slot_count
   int64_t n_units = 0;
   size_t slots_offset = 0;      // merge: slot list; backward: dQ items
 };
@@ -350,6 +351,7 @@ zl_status build_plan_host(const zl_seg_desc* d, int32_t H, zl_dtype dt, int op, 
     MergeTable t = build_merge(d, H);
     p.n_segs = (int32_t)t.segs.size();
     p.n_units = t.units;
+    for (const zl::MergeSeg& m : t.segs) p.max_slots = std::max(p.max_slots, m.slot_count);
     const size_t seg_bytes = t.segs.size() * sizeof(zl::MergeSeg);
     p.slots_offset = (seg_bytes + 255) / 256 * 256;
     p.host.resize(p.slots_offset + t.slots.size() * sizeof(int32_t));
@@ -818,6 +820,7 @@ zl_status zl_lse_merge_ex(const zl_seg_desc* desc, int32_t H, int32_t hd, zl_dty
   p.segs = static_cast<const zl::MergeSeg*>(plan->dev);
   p.slots = reinterpret_cast<const int32_t*>(static_cast<const char*>(plan->dev) + plan->slots_offset);
   p.n_segs = plan->n_segs;
+  p.max_slots = plan->max_slots;
   p.num_heads = H;
   p.n_units = plan->n_units;
   p.slot_stride = (int64_t)sh.total_q * H * hd;

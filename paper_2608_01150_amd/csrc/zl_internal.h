@@ -92,6 +92,7 @@ struct MergeParams {
   const MergeSeg* segs;
   const int32_t* slots;
   int32_t n_segs;
+  int32_t max_slots;     // largest slot_count of the segments
   int32_t num_heads;
   int64_t n_units;
   int64_t slot_stride;
