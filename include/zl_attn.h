@@ -347,7 +347,9 @@ zl_status zl_attn_bwd_noalloc(const zl_seg_desc* desc, int32_t num_heads, int32_
  * Order: cost = q_len * k_len descending, ties by (segment, head, q_start,
  * k_start, range) ascending.  Writes min(n, cap) items to `items` (may be
  * NULL when cap is 0) and the total count to *n.  *tile_m / *tile_n (may be
- * NULL) receive the query / key tile sizes of that schedule.
+ * NULL) receive the query / key tile sizes of that schedule.  A bf16 forward or
+ * dQ launch with so few items that smaller tiles still fit one round on the GPU
+ * runs each item's query rows as halves or quarters of tile_m.
  */
 zl_status zl_plan_dump(const zl_seg_desc* desc, int32_t num_heads, int32_t head_dim, zl_dtype dtype,
                        int32_t op, int32_t* items, size_t cap, size_t* n,

@@ -17,7 +17,11 @@
 // load K, waves 4-7 load V, each fetch's instructions spread over the S
 // MFMAs); a tile is two 64-key steps and one barrier.  A staged tile serves
 // 256 queries, so the staging costs half as much per MFMA as with 128-row
-// items.
+// items.  Launches with few items run tiles of 128 or 64 rows instead, two or
+// four waves sharing each 32 rows (KeySplit in zl_device.h): a tile of 128 keys
+// then takes 3,620 or 2,740 cycles instead of 6,100 (bound by the 64 KB it stages:
+// about 1,450 cycles of load issue and 1,000 of latency), and the parts of a row
+// are combined through LDS at the end.
 //
 // Epilogue: WHOLE items write the final bf16 output and the LSE; SHARD items
 // write the block-normalised partial (fp32, or bf16 on request) and its LSE

@@ -244,6 +244,22 @@ __device__ __forceinline__ float xor32_sum(float v) {
   return __uint_as_float(r[0]) + __uint_as_float(r[1]);
 }
 
+// Sum over each group of N (8 or 16) consecutive lanes, in every lane of it, by
+// DPP moves (no LDS): mirrors of 16 and 8 lanes pair up lanes whose sums are
+// equal afterwards, then the four of a quad are added.
+template <int CTRL>
+__device__ __forceinline__ float dpp_add(float x) {
+  return x + __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(x), CTRL, 0xF, 0xF, true));
+}
+template <int N>
+__device__ __forceinline__ float lanes_sum(float x) {
+  static_assert(N == 8 || N == 16, "lanes per group");
+  if constexpr (N == 16) x = dpp_add<0x140>(x);  // row_mirror
+  x = dpp_add<0x141>(x);                         // row_half_mirror
+  x = dpp_add<0xB1>(x);                          // quad_perm [1,0,3,2]
+  return dpp_add<0x4E>(x);                       // quad_perm [2,3,0,1]
+}
+
 // ------------------------------------------------------------- key split
 // Item idx of a launch whose table items of up to tile_m query rows are split
 // into PARTS sub-items of tile_m / PARTS rows: part idx % PARTS of item
