@@ -184,6 +184,16 @@ class SegDesc:
         ends = [int(a["cu_seqlens_q"][s + 1]) for s in range(len(a["kind"])) if int(a["kind"][s]) == ZL_SHARD]
         self.shard_rows_end = max(ends, default=0)
 
+    def uses_every_k_row(self) -> bool:
+        """Whether the segments' K/V ranges hold every row of K (each range used once, as the backward
+        requires).  False for a descriptor whose indices the library will reject."""
+        a = self._a
+        cu, f = a["cu_seqlens_k"].astype(np.int64), a["kv_first"].astype(np.int64)
+        try:
+            return int((cu[f + a["kv_count"]] - cu[f]).sum()) == self.total_k
+        except (IndexError, ValueError):
+            return False
+
     @classmethod
     def of(cls, w) -> "SegDesc":
         get = (lambda n: w[n]) if isinstance(w, dict) else (lambda n: getattr(w, n))
@@ -453,8 +463,11 @@ def attn_bwd(desc: SegDesc, q, k, v, out, lse, dout, scale: float, dq=None, dk=N
     _need(lse, "lse", (tq, h), torch.float32)
     dev = _same_gpu(q, k, v, out, lse, dout, dq, dk, dv, workspace)
     dq = torch.empty_like(q) if dq is None else dq
-    dk = torch.zeros_like(k) if dk is None else dk
-    dv = torch.zeros_like(v) if dv is None else dv
+    if dk is None or dv is None:
+        # the library writes every row of a range that a segment uses: only others need the zeros
+        new = torch.empty_like if desc.uses_every_k_row() else torch.zeros_like
+        dk = new(k) if dk is None else dk
+        dv = new(v) if dv is None else dv
     if workspace is None:
         workspace = torch.empty(workspace_size(desc, h, d, q.dtype, ZL_OP_BWD), dtype=torch.uint8, device=dev)
     _check(_bwd(desc.ptr(), h, d, _dtype_code(q.dtype), float(scale), _p(q), _p(k), _p(v), _p(out), _p(lse),

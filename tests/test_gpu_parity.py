@@ -337,3 +337,26 @@ def test_forward_running_max_jumps():
     ref = oracle.packed_forward(d, q.double().numpy(), k.double().numpy(), v.double().numpy(), scale)
     np.testing.assert_allclose(to64(out), ref["out"], rtol=0, atol=O_TOL)
     np.testing.assert_allclose(to64(lse), ref["lse"], rtol=0, atol=LSE_TOL)
+
+
+@pytest.mark.parametrize("unused", [False, True])
+def test_backward_allocates_zeros_for_unused_ranges(unused):
+    """dK / dV that the binding allocates: rows of a K/V range that no segment uses are zero, every
+    other row is written."""
+    cu_k = (0, 70, 100, 190) if unused else (0, 70, 160)
+    d = _descs.desc(cu_q=(0, 70, 110), kind=(0, 1), kv_first=(0, 2 if unused else 1), kv_count=(1, 1), cu_k=cu_k,
+                    block_index=(0,) * (len(cu_k) - 1), num_slots=1)
+    H, hd = 2, 64
+    desc = api.SegDesc.of(d)
+    assert desc.uses_every_k_row() != unused
+    q, k, v, do = (t.cuda() for t in _inputs(d, H, hd, torch.bfloat16, 63))
+    out, lse, op, lp = api.attn_fwd(desc, q, k, v, hd ** -0.5)
+    api.lse_merge(desc, op, lp, out, lse)
+    # freed blocks of the gradients' sizes, full of NaN: what an unwritten row would show
+    trash = [torch.full_like(k, float("nan")) for _ in range(4)]
+    del trash
+    dq, dk, dv = api.attn_bwd(desc, q, k, v, out, lse, do, hd ** -0.5)
+    for t in (dq, dk, dv):
+        assert not torch.isnan(t).any()
+    if unused:
+        assert torch.count_nonzero(dk[70:100]) == 0 and torch.count_nonzero(dv[70:100]) == 0
