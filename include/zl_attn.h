@@ -388,7 +388,8 @@ zl_status zl_fill_pack(int32_t num_ranks, int32_t num_fillers, const double* pri
 /*
  * Per-kernel timing with HIP events (off by default).  While enabled, every
  * kernel this library launches is bracketed by two events recorded on the
- * stream it is launched on.  zl_profile_read waits for the pending events of
+ * stream it is launched on (and the backward's dK/dV and dQ, otherwise mostly
+ * one launch, are launched apart, with the same results).  zl_profile_read waits for the pending events of
  * one kernel family, adds their elapsed times to its totals and returns the
  * totals since the last reset.  Kernel ids: ZL_K_FWD, ZL_K_MERGE,
  * ZL_K_BWD_PRE, ZL_K_BWD_DKDV, ZL_K_BWD_DQ, ZL_K_ULYSSES (the four Ulysses

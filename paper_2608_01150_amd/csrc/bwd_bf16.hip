@@ -1,6 +1,7 @@
 // Packed whole+shard attention backward, bf16 inputs, gfx950 MFMA.
 //
-// Three launches on one stream, no atomics (results are deterministic):
+// Three steps on one stream, no atomics (results are deterministic), as a launch
+// each or, in most batches, with 2 and 3 in one launch:
 //   1. preprocess  -D_i = -dO_i . O_i in fp32 for every query row and head
 //                  (the dP MFMAs start their accumulation from it, so they
 //                  produce dP - D directly), and LSE_i in log2 units.
@@ -20,8 +21,9 @@
 //                    dS^T = P^T (dP^T - D)
 //                    dQ^T += K^T dS^T                 MFMA
 //                  A shard row sums its blocks inside one item.
-// Both run one workgroup per CU that takes items one after another from the
-// launch's work queues (zl_device.h).  Q/dO (dK/dV) and K/V (dQ) tiles are
+// 2 and 3 run one workgroup per CU that takes items one after another from the
+// launch's work queues (zl_device.h); in one launch a workgroup that runs out of
+// dK/dV items goes on with dQ items.  Q/dO (dK/dV) and K/V (dQ) tiles are
 // staged row-major (padded pitch, conflict-free) in rotating LDS buffers by
 // direct buffer-to-LDS loads issued ahead of use; the transposed operands
 // (Q^T, dO^T, K^T) come straight from the row-major tiles through LDS
@@ -83,17 +85,33 @@ __global__ __launch_bounds__(NT) void bwd_pre_kernel(BwdParams p) {
 // buffers and tile t+1 is fetched at the start of phase 2t.
 constexpr int kDkdvThreads = 512;
 
+// Workgroup state shared by the item loops: the next item (two slots, see the
+// forward kernel) and the queue in use.
+struct ItemState {
+  int item[2], tries;
+};
+
+// LDS of the item loops, one after another in the same memory.
 template <int D>
-__global__ __launch_bounds__(kDkdvThreads, 1) void bwd_dkdv_kernel(BwdParams p) {
+constexpr int kDkdvLds = 6 * kBwdTileM * Pad<D>::PITCH + 6 * kBwdTileM * 4 + 2 * 4 * 4 * 64 * 16;
+template <int D>
+constexpr int kDqLds = 4 * 2 * kDqTileN * Pad<D>::PITCH;
+
+// Runs dK/dV items: item `first` (-1: none), then claimed ones; `grid` is the
+// number of items that the workgroups started with.
+template <int D>
+__device__ __forceinline__ void dkdv_items(const BwdParams& p, char* lds, ItemState& st, int& parity, int first, int grid) {
   constexpr int BQ = kBwdTileM;                 // 64 queries per tile
   constexpr int PITCH = Pad<D>::PITCH;
   constexpr int TILE = BQ * PITCH;              // bytes of one Q (or dO) tile
   constexpr int NBUF = 3;
   constexpr int NM = D / 8;                     // MFMAs per sub-block and role
-  __shared__ __attribute__((aligned(16))) char qs[NBUF][TILE], dos[NBUF][TILE];
-  __shared__ __attribute__((aligned(16))) float lss[NBUF][BQ], dss[NBUF][BQ];
+  char(*const qs)[TILE] = reinterpret_cast<char(*)[TILE]>(lds);
+  char(*const dos)[TILE] = reinterpret_cast<char(*)[TILE]>(lds + NBUF * TILE);
+  float(*const lss)[BQ] = reinterpret_cast<float(*)[BQ]>(lds + 2 * NBUF * TILE);
+  float(*const dss)[BQ] = lss + NBUF;
   // P/dS exchange: [k%2][key group][word: P h0, P h1, dS h0, dS h1][lane].
-  __shared__ __attribute__((aligned(16))) u32x4 xch[2][4][4][64];
+  u32x4(*const xch)[4][4][64] = reinterpret_cast<u32x4(*)[4][4][64]>(lds + 2 * NBUF * (TILE + BQ * 4));
 
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -137,20 +155,17 @@ __global__ __launch_bounds__(kDkdvThreads, 1) void bwd_dkdv_kernel(BwdParams p) 
   // its own item loop (their registers then need not coexist); both loops
   // pass the same barriers.  Thread 0 (a producer) claims the next item at
   // the start of the current item's last tile and publishes it through
-  // s_item; next_item returns it to every wave, -1 at the end.
-  __shared__ int s_item[2], s_tries;
-  if (tid == 0) s_tries = 0;
-  int parity = 0;
+  // st.item; next_item returns it to every wave, -1 at the end.
+  if (tid == 0) st.tries = 0;
   auto next_item = [&](int pending) __attribute__((always_inline)) {
     const auto* pk = kernargs<BwdParams>();
     if (tid == 0)
-      s_item[parity] = pk->wq_kv ? wq_next(pk->wq_kv, pk->n_kv_items, pk->xcd_chunk, &s_tries, pending) : -1;
+      st.item[parity] = pk->wq_kv ? wq_next(pk->wq_kv, pk->n_kv_items, grid, pk->xcd_chunk, &st.tries, pending) : -1;
     __syncthreads();  // also: both roles are done with this item's LDS
-    const int idx = __builtin_amdgcn_readfirstlane(s_item[parity]);
+    const int idx = __builtin_amdgcn_readfirstlane(st.item[parity]);
     parity ^= 1;
     return idx;
   };
-  const int first = dispatch_item(blockIdx.x, p.n_kv_items, p.xcd_chunk);
 
   if (producer) {
     // ---------------------------------------------------------- producer
@@ -267,7 +282,7 @@ __global__ __launch_bounds__(kDkdvThreads, 1) void bwd_dkdv_kernel(BwdParams p) 
         wait_vmem();  // own loads of tile t+1 landed
         __syncthreads();
         fetch(it, t + 2, (r + 2) % NBUF);
-        if (t == nsteps - 1 && tid == 0 && p.wq_kv && s_tries < 8) pending = wq_claim(p.wq_kv, s_tries);
+        if (t == nsteps - 1 && tid == 0 && p.wq_kv && st.tries < 8) pending = wq_claim(p.wq_kv, st.tries);
         phase(0, (r + 1) % NBUF, 1, r, true, 1);
         __syncthreads();
       };
@@ -282,7 +297,6 @@ __global__ __launch_bounds__(kDkdvThreads, 1) void bwd_dkdv_kernel(BwdParams p) 
       __syncthreads();
       wait_vmem();  // the lookahead loads must land before the LDS is reused
     }
-    if (tid == 0 && p.wq_kv) wq_finish(p.wq_kv);
     return;
   }
 
@@ -441,8 +455,9 @@ __device__ __forceinline__ void dq_store(const __attribute__((address_space(4)))
 // query's parts are plain sums, added in order at the end.
 constexpr int kDqThreads = 512;
 
+// Runs dQ items: item `idx` (-1: none), then claimed ones (see dkdv_items).
 template <int D, int PARTS>
-__global__ __launch_bounds__(kDqThreads, 1) void bwd_dq_kernel(BwdParams p) {
+__device__ __forceinline__ void dq_items(const BwdParams& p, char* lds, ItemState& st, int& parity, int idx, int grid) {
   using Split = KeySplit<PARTS>;
   constexpr int BN = kDqTileN;                  // 64 keys per step
   constexpr int TN = 2 * BN;                    // keys per staged tile: two steps per barrier
@@ -450,18 +465,15 @@ __global__ __launch_bounds__(kDqThreads, 1) void bwd_dq_kernel(BwdParams p) {
   constexpr int TILE = TN * PITCH;
   using Dma = TileDma<D, BN>;                   // one 64-key half of a staged tile
   constexpr int DMA_PER_STEP = Dma::PER_WAVE;   // per wave and half (four waves share a tile)
-  // Two buffers of each tile as separate objects (see the forward kernel).
-  __shared__ __attribute__((aligned(16))) char ks0[TILE], ks1[TILE], vs0[TILE], vs1[TILE];
+  // Two buffers of each tile.
+  char *const ks0 = lds, *const ks1 = lds + TILE, *const vs0 = lds + 2 * TILE, *const vs1 = lds + 3 * TILE;
 
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int ln = lane & 31, g = lane >> 5;
   // Items from the launch's work queues, as in the forward.
-  __shared__ int s_item[2], s_tries;
-  if (tid == 0) s_tries = 0;
   int pending = -1;
-  int parity = 0;
-  for (int idx = dispatch_item(blockIdx.x, p.n_q_items, p.xcd_chunk);;) {
+  while (idx >= 0) {
     const Item it = sub_item<PARTS>(p.q_items, idx, kDqTileM);
     const int H = p.num_heads;
     const int64_t rs = (int64_t)H * D;
@@ -678,7 +690,7 @@ __global__ __launch_bounds__(kDqThreads, 1) void bwd_dq_kernel(BwdParams p) {
     };
 
     auto claim_ahead = [&]() __attribute__((always_inline)) {
-      if (tid == 0 && p.wq_q && s_tries < 8) pending = wq_claim(p.wq_q, s_tries);
+      if (tid == 0 && p.wq_q && st.tries < 8) pending = wq_claim(p.wq_q, st.tries);
     };
 
     // Two buffer sets in rotation, unrolled by two, as in the forward.  An
@@ -736,14 +748,61 @@ __global__ __launch_bounds__(kDqThreads, 1) void bwd_dq_kernel(BwdParams p) {
     }
     if (q_ok && Split::part(wave) == 0) dq_store<D>(kernargs<BwdParams>(), it, qrow, g, dq);
     const auto* pk = kernargs<BwdParams>();
-    if (tid == 0) s_item[parity] = pk->wq_q ? wq_next(pk->wq_q, pk->n_q_items, pk->xcd_chunk, &s_tries, pending) : -1;
+    if (tid == 0)
+      st.item[parity] = pk->wq_q ? wq_next(pk->wq_q, pk->n_q_items, grid, pk->xcd_chunk, &st.tries, pending) : -1;
     pending = -1;
     __syncthreads();  // also: every wave is done with this item's LDS tiles
-    idx = __builtin_amdgcn_readfirstlane(s_item[parity]);
+    idx = __builtin_amdgcn_readfirstlane(st.item[parity]);
     parity ^= 1;
-    if (idx < 0) break;
   }
-  if (tid == 0 && p.wq_q) wq_finish(p.wq_q);
+}
+
+template <int D>
+__global__ __launch_bounds__(kDkdvThreads, 1) void bwd_dkdv_kernel(BwdParams p) {
+  __shared__ __attribute__((aligned(16))) char lds[kDkdvLds<D>];
+  __shared__ ItemState st;
+  int parity = 0;
+  dkdv_items<D>(p, lds, st, parity, dispatch_item(blockIdx.x, p.n_kv_items, p.xcd_chunk), gridDim.x);
+  if (threadIdx.x == 0 && p.wq_kv) wq_finish(p.wq_kv);
+}
+
+template <int D, int PARTS>
+__global__ __launch_bounds__(kDqThreads, 1) void bwd_dq_kernel(BwdParams p) {
+  __shared__ __attribute__((aligned(16))) char lds[kDqLds<D>];
+  __shared__ ItemState st;
+  int parity = 0;
+  if (threadIdx.x == 0) st.tries = 0;
+  dq_items<D, PARTS>(p, lds, st, parity, dispatch_item(blockIdx.x, p.n_q_items, p.xcd_chunk), gridDim.x);
+  if (threadIdx.x == 0 && p.wq_q) wq_finish(p.wq_q);
+}
+
+// Both in one launch: the workgroups run the dK/dV items and go on to the dQ
+// items as they run out, the first n_kv ones starting with a dK/dV item, the
+// rest with a dQ item.
+template <int D, int PARTS>
+__global__ __launch_bounds__(kDkdvThreads, 1) void bwd_fused_kernel(BwdParams p) {
+  static_assert(kDkdvThreads == kDqThreads, "one workgroup runs both");
+  __shared__ __attribute__((aligned(16))) char lds[kDkdvLds<D> > kDqLds<D> ? kDkdvLds<D> : kDqLds<D>];
+  __shared__ ItemState st;
+  int parity = 0, first_q = -1;
+  const int b = blockIdx.x, grid_kv = min((int)gridDim.x, p.n_kv_items), grid_q = (int)gridDim.x - grid_kv;
+  if (b < grid_kv) {
+    dkdv_items<D>(p, lds, st, parity, dispatch_item(b, p.n_kv_items, p.xcd_chunk), grid_kv);
+    if (p.wq_q) {
+      if (threadIdx.x == 0) {
+        st.tries = 0;
+        st.item[parity] = wq_next(p.wq_q, p.n_q_items, grid_q, p.xcd_chunk, &st.tries, -1);
+      }
+      __syncthreads();
+      first_q = __builtin_amdgcn_readfirstlane(st.item[parity]);
+      parity ^= 1;
+    }
+  } else {
+    if (threadIdx.x == 0) st.tries = 0;
+    first_q = dispatch_item(b - grid_kv, p.n_q_items, p.xcd_chunk);
+  }
+  dq_items<D, PARTS>(p, lds, st, parity, first_q, grid_q);
+  if (threadIdx.x == 0 && p.wq_q) wq_finish2(p.wq_kv, p.wq_q);
 }
 
 }  // namespace
@@ -771,6 +830,21 @@ hipError_t launch_dq_d(const BwdParams& p, hipStream_t s) {
   return p.split_q == 0 ? launch_dq<D, 1>(p, s) : p.split_q == 1 ? launch_dq<D, 2>(p, s) : launch_dq<D, 4>(p, s);
 }
 
+template <int D, int PARTS>
+hipError_t launch_fused(BwdParams p, hipStream_t s) {
+  const int n = p.n_kv_items + p.n_q_items;
+  const int grid = launch_grid(reinterpret_cast<const void*>(bwd_fused_kernel<D, PARTS>), kDqThreads, n, p.wq_q);
+  if (grid < 0) return hipErrorInvalidValue;
+  if (grid == n) p.wq_kv = p.wq_q = nullptr;  // a single round: nothing to claim
+  hipLaunchKernelGGL((bwd_fused_kernel<D, PARTS>), dim3(grid), dim3(kDqThreads), 0, s, p);
+  return hipGetLastError();
+}
+
+template <int D>
+hipError_t launch_fused_d(const BwdParams& p, hipStream_t s) {
+  return p.split_q == 0 ? launch_fused<D, 1>(p, s) : p.split_q == 1 ? launch_fused<D, 2>(p, s) : launch_fused<D, 4>(p, s);
+}
+
 hipError_t launch_bwd_bf16(const BwdParams& p, int head_dim, int stage, hipStream_t s) {
   const dim3 block(NT);
   if (stage == 0) {
@@ -783,6 +857,9 @@ hipError_t launch_bwd_bf16(const BwdParams& p, int head_dim, int stage, hipStrea
   } else if (stage == 1) {
     if (p.n_kv_items == 0) return hipSuccess;
     return head_dim == 128 ? launch_dkdv<128>(p, s) : launch_dkdv<64>(p, s);
+  } else if (stage == 3) {
+    if (p.n_kv_items + p.n_q_items == 0) return hipSuccess;
+    return head_dim == 128 ? launch_fused_d<128>(p, s) : launch_fused_d<64>(p, s);
   } else {
     if (p.n_q_items == 0) return hipSuccess;
     return head_dim == 128 ? launch_dq_d<128>(p, s) : launch_dq_d<64>(p, s);

@@ -549,7 +549,7 @@ __global__ __launch_bounds__(NT, 1) void fwd_bf16_kernel(FwdParams p) {
     }
     fwd_store<D>(kernargs<FwdParams>(), it, qr, q_ok && Split::part(wave) == 0, g, o, m_run, l_part, r_run);
     const auto* pk = kernargs<FwdParams>();
-    if (tid == 0) s_item[parity] = pk->wq ? wq_next(pk->wq, pk->n_items, pk->xcd_chunk, &s_tries, pending) : -1;
+    if (tid == 0) s_item[parity] = pk->wq ? wq_next(pk->wq, pk->n_items, gridDim.x, pk->xcd_chunk, &s_tries, pending) : -1;
     pending = -1;
     __syncthreads();  // also: every wave is done with this item's LDS tiles
     idx = __builtin_amdgcn_readfirstlane(s_item[parity]);

@@ -327,17 +327,17 @@ __device__ __forceinline__ int wq_claim(int* ctr, int tries) { return atomicAdd(
 
 // Work-table index of this workgroup's next item, or -1 when every queue is
 // empty.  *tries (workgroup state, in LDS) is the queue in use as an offset from
-// the workgroup's XCD (8: all empty); pending is a claim from wq_claim on that
+// the workgroup's XCD (8: all empty), grid the number of positions that the first
+// round took; pending is a claim from wq_claim on that
 // queue, or -1.  When the claim finds its queue empty, one look at all eight
 // counters picks the next queue that still holds items: claiming from each in
 // turn made every workgroup wait for up to eight atomics one after another when
 // it ran out of work (3 to 12 us at the end of a launch; two round trips now).
 // A queue whose claim fails stays empty, so the loop ends after at most nine
 // looks.
-__device__ __forceinline__ int wq_next(int* ctr, int n, int chunk, int* tries, int pending) {
+__device__ __forceinline__ int wq_next(int* ctr, int n, int grid, int chunk, int* tries, int pending) {
   int t = *tries;
   if (t >= 8) return -1;
-  const int grid = (int)gridDim.x;
   const int xcd = xcd_id();
   auto len = [&](int y) { return (n - y + 7) >> 3; };        // positions y + 8k below n
   auto first = [&](int y) { return (grid - y + 7) >> 3; };   // of those, taken by the first round
@@ -370,6 +370,18 @@ __device__ __forceinline__ void wq_finish(int* ctr) {
   if ((unsigned)atomicAdd(&ctr[8], 1) == gridDim.x - 1u) {
 #pragma unroll
     for (int y = 0; y < 9; ++y) atomicExch(&ctr[y], 0);
+  }
+}
+
+// The same for a launch that uses two counter blocks: the first counts the
+// workgroups, both are reset.
+__device__ __forceinline__ void wq_finish2(int* ctr, int* ctr2) {
+  if ((unsigned)atomicAdd(&ctr[8], 1) == gridDim.x - 1u) {
+#pragma unroll
+    for (int y = 0; y < 9; ++y) {
+      atomicExch(&ctr[y], 0);
+      atomicExch(&ctr2[y], 0);
+    }
   }
 }
 

@@ -257,17 +257,42 @@ std::vector<zl::Item> build_items(const zl_seg_desc* d, int32_t H, int op, TileC
 // of full tiles against 3 of halves: 5,461 tokens +1%, 6,400 -6%, 8,160 -1.7%;
 // 3 x 1560 tokens, 1 round against 2: +17%).  Measured: one 1560-token image, 12
 // heads, 84 items, as halves: forward 44.7 -> 33.0 us, dQ 54.6 -> 39.1 us; one
-// 448-token image as quarters: forward 16.4 -> 13.0 us.  Only the items' rows
-// count, so a shard's ring step splits as the backward of all its blocks does.
+// 448-token image as quarters: forward 16.4 -> 13.0 us.
+size_t sub_items(const std::vector<zl::Item>& items, int tile_m, int split) {
+  const int m = tile_m >> split;
+  size_t n = 0;
+  for (const zl::Item& it : items) n += (size_t)((it.q_len + m - 1) / m);
+  return n;
+}
+
 int choose_split(const std::vector<zl::Item>& items, int tile_m) {
   const size_t slots = (size_t)zl::device_cus();
-  for (int split = 2; split > 0 && items.size() <= slots; --split) {
-    const int m = tile_m >> split;
-    size_t n = 0;
-    for (const zl::Item& it : items) n += (size_t)((it.q_len + m - 1) / m);
-    if (n <= slots) return split;
-  }
+  if (items.size() > slots) return 0;
+  for (int split = 2; split > 0; --split)
+    if (sub_items(items, tile_m, split) <= slots) return split;
   return 0;
+}
+
+// The backward's dK/dV and dQ items in one launch or two, and the dQ split.
+// Both need only the preprocess, so one launch lets the workgroups that run out
+// of dK/dV items go on with dQ items: the chip idles in one last round instead
+// of two, and a small batch runs both side by side.  Measured (forward and
+// backward): one 1560-token image, 12 heads, 156 + 84 items in one round: 109 ->
+// 92 us; 40 heads, 520 + 280 items: 336 -> 290 us; sixteen images, 2,496 + 1,344
+// items: 1,159 -> 1,130 us; the mixed image-video batch, 16,400 + 8,400 items: no
+// difference.  Two launches stay better where the dQ items split into a single
+// round by themselves but the two do not fit one round together (4 x 448 tokens, 12
+// heads, 192 + 96 items: 58.5 us apart with halves, 62.2 in one launch).
+void choose_bwd(const std::vector<zl::Item>& kv, const std::vector<zl::Item>& q, int32_t* split, bool* fused) {
+  const size_t slots = (size_t)zl::device_cus();
+  *fused = true;
+  if (kv.size() + q.size() <= slots) {
+    for (*split = 2; *split > 0; --*split)
+      if (kv.size() + sub_items(q, zl::kDqTileM, *split) <= slots) return;
+    return;
+  }
+  *split = choose_split(q, zl::kDqTileM);
+  *fused = *split == 0;
 }
 
 struct MergeTable {
@@ -298,7 +323,8 @@ struct Plan {
   std::vector<char> host;       // host copy (source of the upload)
   int32_t n_items = 0;          // forward items, or backward dK/dV items
   int32_t n_items2 = 0;         // backward dQ items
-  int32_t split = 0;            // choose_split of the forward or dQ items (bf16)
+  int32_t split = 0;            // how the forward or dQ query tiles are split (bf16, see choose_split)
+  bool fused = false;           // backward: dK/dV and dQ items in one launch
   int32_t n_segs = 0;
   int32_t max_slots = 0;        // merge: largest slot_count
   int64_t n_units = 0;
@@ -365,7 +391,7 @@ zl_status build_plan_host(const zl_seg_desc* d, int32_t H, zl_dtype dt, int op, 
       return fail(ZL_ERR_UNSUPPORTED, "too many work items");
     p.n_items = (int32_t)kv.size();
     p.n_items2 = (int32_t)qi.size();
-    p.split = choose_split(qi, zl::kDqTileM);
+    choose_bwd(kv, qi, &p.split, &p.fused);
     p.slots_offset = align256(kv.size() * sizeof(zl::Item));
     p.host.assign(p.slots_offset + qi.size() * sizeof(zl::Item), 0);
     if (!kv.empty()) std::memcpy(p.host.data(), kv.data(), kv.size() * sizeof(zl::Item));
@@ -515,16 +541,16 @@ std::mutex g_prof_mu;
 bool g_prof_on = false;
 ProfSlot g_prof[ZL_K_COUNT];
 
+bool profiling() {
+  std::lock_guard<std::mutex> lk(g_prof_mu);
+  return g_prof_on;
+}
+
 // Runs `launch` (which enqueues one kernel on `s`), bracketed by events when
 // profiling is on.
 template <class F>
 hipError_t timed(int kid, hipStream_t s, F&& launch) {
-  bool on;
-  {
-    std::lock_guard<std::mutex> lk(g_prof_mu);
-    on = g_prof_on;
-  }
-  if (!on) return launch();
+  if (!profiling()) return launch();
   hipEvent_t a = nullptr, b = nullptr;
   if (hipEventCreate(&a) != hipSuccess) return hipErrorOutOfMemory;
   if (hipEventCreate(&b) != hipSuccess) {
@@ -881,7 +907,7 @@ zl_status validate_bwd(const BwdCall& c, Shape* sh) {
 // memory.  No early return for Tq = 0: the ranges of a SHARD without query
 // rows still get their (zero) dK/dV.
 zl_status launch_bwd(const BwdCall& c, const Shape& sh, const void* tables, size_t q_offset, int32_t n_kv,
-                     int32_t n_q, int32_t split_q, void* workspace, hipStream_t s) {
+                     int32_t n_q, int32_t split_q, bool plan_fused, void* workspace, hipStream_t s) {
   const bool first = !c.step || (c.flags & ZL_STEP_FIRST), last = !c.step || (c.flags & ZL_STEP_LAST);
   zl::BwdParams p{};
   p.q = c.q;
@@ -900,7 +926,7 @@ zl_status launch_bwd(const BwdCall& c, const Shape& sh, const void* tables, size
   p.n_kv_items = n_kv;
   p.q_items = reinterpret_cast<const zl::Item*>(base + q_offset);
   p.split_q = split_q;
-  p.n_q_items = n_q << p.split_q;
+  p.n_q_items = n_q << split_q;
   p.num_heads = c.H;
   p.total_q = sh.total_q;
   p.scale = c.scale;
@@ -917,6 +943,9 @@ zl_status launch_bwd(const BwdCall& c, const Shape& sh, const void* tables, size
   p.wq_q = wq ? wq + 2 * zl::kWqPerLaunch : nullptr;
   const int hd = c.hd;
   hipError_t e = timed(ZL_K_BWD_PRE, s, [&] { return zl::launch_bwd_bf16(p, hd, 0, s); });
+  // With profiling on the two kernels run apart, so that each is timed.
+  if (e == hipSuccess && plan_fused && !profiling())
+    return hip_status(zl::launch_bwd_bf16(p, hd, 3, s), "backward launch");
   if (e == hipSuccess) e = timed(ZL_K_BWD_DKDV, s, [&] { return zl::launch_bwd_bf16(p, hd, 1, s); });
   if (e == hipSuccess) e = timed(ZL_K_BWD_DQ, s, [&] { return zl::launch_bwd_bf16(p, hd, 2, s); });
   return hip_status(e, "backward launch");
@@ -935,7 +964,8 @@ zl_status attn_bwd_impl(const BwdCall& c, void* workspace, size_t ws_bytes, void
   Plan* plan = nullptr;
   hipStream_t s = static_cast<hipStream_t>(stream);
   if ((st = get_plan(c.desc, c.H, c.hd, c.dt, c.step ? kPlanBwdStep : ZL_OP_BWD, s, &plan)) != ZL_OK) return st;
-  return launch_bwd(c, sh, plan->dev, plan->slots_offset, plan->n_items, plan->n_items2, plan->split, workspace, s);
+  return launch_bwd(c, sh, plan->dev, plan->slots_offset, plan->n_items, plan->n_items2, plan->split, plan->fused,
+                    workspace, s);
 }
 
 }  // namespace
@@ -964,7 +994,7 @@ zl_status attn_bwd_scratch(const zl_seg_desc* desc, int32_t H, int32_t hd, zl_dt
   if (!hp->host.empty() &&
       hipMemcpyAsync(base, hp->host.data(), hp->host.size(), hipMemcpyHostToDevice, s) != hipSuccess)
     return fail(ZL_ERR_HIP, "copy of the work tables into the scratch failed");
-  return launch_bwd(c, sh, base, hp->slots_offset, hp->n_items, hp->n_items2, hp->split,
+  return launch_bwd(c, sh, base, hp->slots_offset, hp->n_items, hp->n_items2, hp->split, hp->fused,
                     static_cast<char*>(base) + tables, s);
 }
 

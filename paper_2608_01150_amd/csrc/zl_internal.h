@@ -181,7 +181,7 @@ zl_status attn_bwd_scratch(const zl_seg_desc* desc, int32_t H, int32_t hd, zl_dt
                            const void* k, const void* v, const void* out, const float* lse, const void* dout, void* dq,
                            void* dk, void* dv, size_t scratch_bytes, ScratchFn acquire, void* stream);
 hipError_t launch_ulysses(const UlyssesParams& p, int op, int head_dim, hipStream_t s);
-// stage 0: preprocess (D), 1: dK/dV, 2: dQ
+// stage 0: preprocess (D), 1: dK/dV, 2: dQ, 3: dK/dV and dQ in one launch
 hipError_t launch_bwd_bf16(const BwdParams& p, int head_dim, int stage, hipStream_t s);
 
 }  // namespace zl

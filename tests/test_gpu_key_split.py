@@ -1,7 +1,8 @@
 """Query tiles of 256, 128 and 64 rows (forward and dQ) at their edges against
 the fp64 oracle.  The library picks the tile by the launch's size: few heads
 give tiles of 64 rows (four waves share a row group), tens of heads 128, and
-hundreds of items whole tiles of 256; the oracle's result is the same.
+hundreds of items whole tiles of 256; the backward runs dK/dV and dQ in one
+launch or two.  The oracle's result is the same.
 Bounds as in the other parity tests."""
 import pytest
 import torch
@@ -33,9 +34,10 @@ def test_tile_edges(heads, hd):
     run_and_compare(d, heads, hd, torch.bfloat16, 60 + heads + hd)
 
 
-@pytest.mark.parametrize("heads", [2, 20, 160])
+@pytest.mark.parametrize("heads", [2, 20, 30, 160])
 def test_one_long_segment(heads):
-    # one segment: 3 tiles of 256 rows, the last one ragged; several 128-key tiles
+    # one segment: 3 tiles of 256 rows, the last one ragged; several 128-key tiles.  The backward's dK/dV
+    # and dQ run in one launch, in a single round with quarters, halves and whole tiles, then in rounds.
     d = _descs.desc(cu_q=(0, 523), kind=(0,), kv_first=(0,), kv_count=(1,), cu_k=(0, 523), block_index=(0,), num_slots=0)
     run_and_compare(d, heads, 128, torch.bfloat16, 70 + heads)
 
@@ -56,3 +58,27 @@ def test_scores_jump_across_parts():
     ref = oracle.packed_forward(d, *(t.double().numpy() for t in (q, k, v)), hd ** -0.5)
     assert np.abs(to64(out) - ref["out"]).max() <= 2e-2
     assert np.abs(to64(lse) - ref["lse"]).max() <= 1e-3
+
+
+def test_profiled_backward_has_the_same_bits():
+    """With profiling on, dK/dV and dQ run as two launches: the same items, the same results."""
+    from tests._gpu import api
+    d = _descs.mixed_small()
+    H, hd = 40, 128
+    desc = api.SegDesc.of(d)
+    g = torch.Generator().manual_seed(82)
+    tq, tk = d["cu_seqlens_q"][-1], d["cu_seqlens_k"][-1]
+    q, k, v, do = (torch.randn((n, H, hd), generator=g).to(torch.bfloat16).cuda() for n in (tq, tk, tk, tq))
+    out, lse, op, lp = api.attn_fwd(desc, q, k, v, hd ** -0.5)
+    api.lse_merge(desc, op, lp, out, lse)
+    one = api.attn_bwd(desc, q, k, v, out, lse, do, hd ** -0.5)
+    api.profile_reset()
+    api.profile_enable(True)
+    try:
+        two = api.attn_bwd(desc, q, k, v, out, lse, do, hd ** -0.5)
+    finally:
+        api.profile_enable(False)
+    assert api.profile_read(api.ZL_K_BWD_DQ)[1] == 1 and api.profile_read(api.ZL_K_BWD_DKDV)[1] == 1
+    api.profile_reset()
+    for a, b in zip(one, two):
+        assert torch.equal(a, b)
