@@ -23,7 +23,7 @@
 //                  A shard row sums its blocks inside one item.
 // 2 and 3 run one workgroup per CU that takes items one after another from the
 // launch's work queues (zl_device.h); in one launch a workgroup that runs out of
-// dK/dV items goes on with dQ items.  Q/dO (dK/dV) and K/V (dQ) tiles are
+// dQ items goes on with dK/dV items.  Q/dO (dK/dV) and K/V (dQ) tiles are
 // staged row-major (padded pitch, conflict-free) in rotating LDS buffers by
 // direct buffer-to-LDS loads issued ahead of use; the transposed operands
 // (Q^T, dO^T, K^T) come straight from the row-major tiles through LDS
@@ -156,7 +156,6 @@ __device__ __forceinline__ void dkdv_items(const BwdParams& p, char* lds, ItemSt
   // pass the same barriers.  Thread 0 (a producer) claims the next item at
   // the start of the current item's last tile and publishes it through
   // st.item; next_item returns it to every wave, -1 at the end.
-  if (tid == 0) st.tries = 0;
   auto next_item = [&](int pending) __attribute__((always_inline)) {
     const auto* pk = kernargs<BwdParams>();
     if (tid == 0)
@@ -762,6 +761,7 @@ __global__ __launch_bounds__(kDkdvThreads, 1) void bwd_dkdv_kernel(BwdParams p) 
   __shared__ __attribute__((aligned(16))) char lds[kDkdvLds<D>];
   __shared__ ItemState st;
   int parity = 0;
+  if (threadIdx.x == 0) st.tries = 0;
   dkdv_items<D>(p, lds, st, parity, dispatch_item(blockIdx.x, p.n_kv_items, p.xcd_chunk), gridDim.x);
   if (threadIdx.x == 0 && p.wq_kv) wq_finish(p.wq_kv);
 }
@@ -776,32 +776,37 @@ __global__ __launch_bounds__(kDqThreads, 1) void bwd_dq_kernel(BwdParams p) {
   if (threadIdx.x == 0 && p.wq_q) wq_finish(p.wq_q);
 }
 
-// Both in one launch: the workgroups run the dK/dV items and go on to the dQ
-// items as they run out, the first n_kv ones starting with a dK/dV item, the
-// rest with a dQ item.
-template <int D, int PARTS>
+// Both in one launch: the workgroups run the items of one kind and go on to the
+// other kind as they run out; the first ones start with the first kind, the rest
+// of the grid with the second.  DQ_FIRST says which is first (see choose_bwd).
+template <int D, int PARTS, bool DQ_FIRST>
 __global__ __launch_bounds__(kDkdvThreads, 1) void bwd_fused_kernel(BwdParams p) {
   static_assert(kDkdvThreads == kDqThreads, "one workgroup runs both");
   __shared__ __attribute__((aligned(16))) char lds[kDkdvLds<D> > kDqLds<D> ? kDkdvLds<D> : kDqLds<D>];
   __shared__ ItemState st;
-  int parity = 0, first_q = -1;
-  const int b = blockIdx.x, grid_kv = min((int)gridDim.x, p.n_kv_items), grid_q = (int)gridDim.x - grid_kv;
-  if (b < grid_kv) {
-    dkdv_items<D>(p, lds, st, parity, dispatch_item(b, p.n_kv_items, p.xcd_chunk), grid_kv);
+  int parity = 0;
+  const int n1 = DQ_FIRST ? p.n_q_items : p.n_kv_items, n2 = DQ_FIRST ? p.n_kv_items : p.n_q_items;
+  const int b = blockIdx.x, grid1 = min((int)gridDim.x, n1), grid2 = (int)gridDim.x - grid1;
+  if (threadIdx.x == 0) st.tries = 0;
+  int second = -1;  // this workgroup's first item of the second kind
+  if (b < grid1) {
+    const int first = dispatch_item(b, n1, p.xcd_chunk);
+    if constexpr (DQ_FIRST) dq_items<D, PARTS>(p, lds, st, parity, first, grid1);
+    else dkdv_items<D>(p, lds, st, parity, first, grid1);
     if (p.wq_q) {
       if (threadIdx.x == 0) {
         st.tries = 0;
-        st.item[parity] = wq_next(p.wq_q, p.n_q_items, grid_q, p.xcd_chunk, &st.tries, -1);
+        st.item[parity] = wq_next(DQ_FIRST ? p.wq_kv : p.wq_q, n2, grid2, p.xcd_chunk, &st.tries, -1);
       }
       __syncthreads();
-      first_q = __builtin_amdgcn_readfirstlane(st.item[parity]);
+      second = __builtin_amdgcn_readfirstlane(st.item[parity]);
       parity ^= 1;
     }
   } else {
-    if (threadIdx.x == 0) st.tries = 0;
-    first_q = dispatch_item(b - grid_kv, p.n_q_items, p.xcd_chunk);
+    second = dispatch_item(b - grid1, n2, p.xcd_chunk);
   }
-  dq_items<D, PARTS>(p, lds, st, parity, first_q, grid_q);
+  if constexpr (DQ_FIRST) dkdv_items<D>(p, lds, st, parity, second, grid2);
+  else dq_items<D, PARTS>(p, lds, st, parity, second, grid2);
   if (threadIdx.x == 0 && p.wq_q) wq_finish2(p.wq_kv, p.wq_q);
 }
 
@@ -830,19 +835,24 @@ hipError_t launch_dq_d(const BwdParams& p, hipStream_t s) {
   return p.split_q == 0 ? launch_dq<D, 1>(p, s) : p.split_q == 1 ? launch_dq<D, 2>(p, s) : launch_dq<D, 4>(p, s);
 }
 
-template <int D, int PARTS>
+template <int D, int PARTS, bool DQ_FIRST>
 hipError_t launch_fused(BwdParams p, hipStream_t s) {
   const int n = p.n_kv_items + p.n_q_items;
-  const int grid = launch_grid(reinterpret_cast<const void*>(bwd_fused_kernel<D, PARTS>), kDqThreads, n, p.wq_q);
+  const int grid =
+      launch_grid(reinterpret_cast<const void*>(bwd_fused_kernel<D, PARTS, DQ_FIRST>), kDqThreads, n, p.wq_q);
   if (grid < 0) return hipErrorInvalidValue;
   if (grid == n) p.wq_kv = p.wq_q = nullptr;  // a single round: nothing to claim
-  hipLaunchKernelGGL((bwd_fused_kernel<D, PARTS>), dim3(grid), dim3(kDqThreads), 0, s, p);
+  hipLaunchKernelGGL((bwd_fused_kernel<D, PARTS, DQ_FIRST>), dim3(grid), dim3(kDqThreads), 0, s, p);
   return hipGetLastError();
 }
 
+// dQ goes first only in launches of several rounds, which run whole tiles.
 template <int D>
 hipError_t launch_fused_d(const BwdParams& p, hipStream_t s) {
-  return p.split_q == 0 ? launch_fused<D, 1>(p, s) : p.split_q == 1 ? launch_fused<D, 2>(p, s) : launch_fused<D, 4>(p, s);
+  if (p.dq_first && p.split_q == 0) return launch_fused<D, 1, true>(p, s);
+  return p.split_q == 0   ? launch_fused<D, 1, false>(p, s)
+         : p.split_q == 1 ? launch_fused<D, 2, false>(p, s)
+                          : launch_fused<D, 4, false>(p, s);
 }
 
 hipError_t launch_bwd_bf16(const BwdParams& p, int head_dim, int stage, hipStream_t s) {

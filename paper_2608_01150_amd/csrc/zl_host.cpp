@@ -275,7 +275,7 @@ int choose_split(const std::vector<zl::Item>& items, int tile_m) {
 
 // The backward's dK/dV and dQ items in one launch or two, and the dQ split.
 // Both need only the preprocess, so one launch lets the workgroups that run out
-// of dK/dV items go on with dQ items: the chip idles in one last round instead
+// of one kind go on with the other: the chip idles in one last round instead
 // of two, and a small batch runs both side by side.  Measured (forward and
 // backward): one 1560-token image, 12 heads, 156 + 84 items in one round: 109 ->
 // 92 us; 40 heads, 520 + 280 items: 336 -> 290 us; sixteen images, 2,496 + 1,344
@@ -283,16 +283,32 @@ int choose_split(const std::vector<zl::Item>& items, int tile_m) {
 // difference.  Two launches stay better where the dQ items split into a single
 // round by themselves but the two do not fit one round together (4 x 448 tokens, 12
 // heads, 192 + 96 items: 58.5 us apart with halves, 62.2 in one launch).
-void choose_bwd(const std::vector<zl::Item>& kv, const std::vector<zl::Item>& q, int32_t* split, bool* fused) {
+//
+// In one launch the kind with the longer items goes first, so that the shorter
+// ones even out the end.  dQ items run over a segment's whole key range: with a
+// shard's many blocks they are several times the dK/dV items (a 4,095-row shard
+// against 32,760 gathered keys, 12 heads: 192 dQ items of 1.1 ms, 3,096 dK/dV items
+// of 0.12 ms; 3,552 us with dK/dV first, 3,315 with dQ first).  Where the two are
+// within a factor of two the order makes 1 to 2% either way, mostly for dK/dV first.
+struct BwdPlan {
+  int32_t split = 0;
+  bool fused = true, dq_first = false;
+};
+
+BwdPlan choose_bwd(const std::vector<zl::Item>& kv, const std::vector<zl::Item>& q) {
   const size_t slots = (size_t)zl::device_cus();
-  *fused = true;
+  BwdPlan b;
   if (kv.size() + q.size() <= slots) {
-    for (*split = 2; *split > 0; --*split)
-      if (kv.size() + sub_items(q, zl::kDqTileM, *split) <= slots) return;
-    return;
+    for (b.split = 2; b.split > 0; --b.split)
+      if (kv.size() + sub_items(q, zl::kDqTileM, b.split) <= slots) break;
+    return b;
   }
-  *split = choose_split(q, zl::kDqTileM);
-  *fused = *split == 0;
+  b.split = choose_split(q, zl::kDqTileM);
+  b.fused = b.split == 0;
+  // both lists are in order of decreasing q_len * k_len; MFMA FLOPs per pair are 8 d and 6 d
+  if (!kv.empty() && !q.empty())
+    b.dq_first = 6. * q[0].q_len * q[0].k_len >= 2. * (8. * kv[0].q_len * kv[0].k_len);
+  return b;
 }
 
 struct MergeTable {
@@ -324,7 +340,8 @@ struct Plan {
   int32_t n_items = 0;          // forward items, or backward dK/dV items
   int32_t n_items2 = 0;         // backward dQ items
   int32_t split = 0;            // how the forward or dQ query tiles are split (bf16, see choose_split)
-  bool fused = false;           // backward: dK/dV and dQ items in one launch
+  bool fused = false;           // backward: dK/dV and dQ items in one launch,
+  bool dq_first = false;        // the dQ items first
   int32_t n_segs = 0;
   int32_t max_slots = 0;        // merge: largest slot_count
   int64_t n_units = 0;
@@ -391,7 +408,10 @@ zl_status build_plan_host(const zl_seg_desc* d, int32_t H, zl_dtype dt, int op, 
       return fail(ZL_ERR_UNSUPPORTED, "too many work items");
     p.n_items = (int32_t)kv.size();
     p.n_items2 = (int32_t)qi.size();
-    choose_bwd(kv, qi, &p.split, &p.fused);
+    const BwdPlan b = choose_bwd(kv, qi);
+    p.split = b.split;
+    p.fused = b.fused;
+    p.dq_first = b.dq_first;
     p.slots_offset = align256(kv.size() * sizeof(zl::Item));
     p.host.assign(p.slots_offset + qi.size() * sizeof(zl::Item), 0);
     if (!kv.empty()) std::memcpy(p.host.data(), kv.data(), kv.size() * sizeof(zl::Item));
@@ -902,12 +922,12 @@ zl_status validate_bwd(const BwdCall& c, Shape* sh) {
 }
 
 
-// Enqueues the three backward kernels.  tables: the dK/dV items, then (at
-// q_offset bytes) the dQ items, split by split_q; workspace: bwd_workspace_bytes of device
+// Enqueues the backward kernels.  tables: the plan's dK/dV items, then (at
+// slots_offset bytes) its dQ items, on the device; workspace: bwd_workspace_bytes of device
 // memory.  No early return for Tq = 0: the ranges of a SHARD without query
 // rows still get their (zero) dK/dV.
-zl_status launch_bwd(const BwdCall& c, const Shape& sh, const void* tables, size_t q_offset, int32_t n_kv,
-                     int32_t n_q, int32_t split_q, bool plan_fused, void* workspace, hipStream_t s) {
+zl_status launch_bwd(const BwdCall& c, const Shape& sh, const Plan& plan, const void* tables, void* workspace,
+                     hipStream_t s) {
   const bool first = !c.step || (c.flags & ZL_STEP_FIRST), last = !c.step || (c.flags & ZL_STEP_LAST);
   zl::BwdParams p{};
   p.q = c.q;
@@ -923,10 +943,11 @@ zl_status launch_bwd(const BwdCall& c, const Shape& sh, const void* tables, size
   p.lse2 = reinterpret_cast<float*>(static_cast<char*>(workspace) + align256((size_t)sh.total_q * c.H * sizeof(float)));
   const char* base = static_cast<const char*>(tables);
   p.kv_items = reinterpret_cast<const zl::Item*>(base);
-  p.n_kv_items = n_kv;
-  p.q_items = reinterpret_cast<const zl::Item*>(base + q_offset);
-  p.split_q = split_q;
-  p.n_q_items = n_q << split_q;
+  p.n_kv_items = plan.n_items;
+  p.q_items = reinterpret_cast<const zl::Item*>(base + plan.slots_offset);
+  p.split_q = plan.split;
+  p.n_q_items = plan.n_items2 << plan.split;
+  p.dq_first = plan.dq_first ? 1 : 0;
   p.num_heads = c.H;
   p.total_q = sh.total_q;
   p.scale = c.scale;
@@ -944,7 +965,7 @@ zl_status launch_bwd(const BwdCall& c, const Shape& sh, const void* tables, size
   const int hd = c.hd;
   hipError_t e = timed(ZL_K_BWD_PRE, s, [&] { return zl::launch_bwd_bf16(p, hd, 0, s); });
   // With profiling on the two kernels run apart, so that each is timed.
-  if (e == hipSuccess && plan_fused && !profiling())
+  if (e == hipSuccess && plan.fused && !profiling())
     return hip_status(zl::launch_bwd_bf16(p, hd, 3, s), "backward launch");
   if (e == hipSuccess) e = timed(ZL_K_BWD_DKDV, s, [&] { return zl::launch_bwd_bf16(p, hd, 1, s); });
   if (e == hipSuccess) e = timed(ZL_K_BWD_DQ, s, [&] { return zl::launch_bwd_bf16(p, hd, 2, s); });
@@ -964,8 +985,7 @@ zl_status attn_bwd_impl(const BwdCall& c, void* workspace, size_t ws_bytes, void
   Plan* plan = nullptr;
   hipStream_t s = static_cast<hipStream_t>(stream);
   if ((st = get_plan(c.desc, c.H, c.hd, c.dt, c.step ? kPlanBwdStep : ZL_OP_BWD, s, &plan)) != ZL_OK) return st;
-  return launch_bwd(c, sh, plan->dev, plan->slots_offset, plan->n_items, plan->n_items2, plan->split, plan->fused,
-                    workspace, s);
+  return launch_bwd(c, sh, *plan, plan->dev, workspace, s);
 }
 
 }  // namespace
@@ -994,8 +1014,7 @@ zl_status attn_bwd_scratch(const zl_seg_desc* desc, int32_t H, int32_t hd, zl_dt
   if (!hp->host.empty() &&
       hipMemcpyAsync(base, hp->host.data(), hp->host.size(), hipMemcpyHostToDevice, s) != hipSuccess)
     return fail(ZL_ERR_HIP, "copy of the work tables into the scratch failed");
-  return launch_bwd(c, sh, base, hp->slots_offset, hp->n_items, hp->n_items2, hp->split, hp->fused,
-                    static_cast<char*>(base) + tables, s);
+  return launch_bwd(c, sh, *hp, base, static_cast<char*>(base) + tables, s);
 }
 
 }  // namespace zl

@@ -116,6 +116,7 @@ struct BwdParams {
   const Item* q_items;         // dQ items: one query tile against every key of its segment
   int32_t n_q_items;           // sub-items: (table items) << split_q
   int32_t split_q;
+  int32_t dq_first;            // one launch for both: dQ items before dK/dV items
   int32_t num_heads;
   int64_t total_q;             // Tq
   float scale;

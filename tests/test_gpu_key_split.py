@@ -82,3 +82,13 @@ def test_profiled_backward_has_the_same_bits():
     api.profile_reset()
     for a, b in zip(one, two):
         assert torch.equal(a, b)
+
+
+@pytest.mark.parametrize("hd", [64, 128])
+def test_long_dq_items_first(hd):
+    """A shard of few rows against many blocks, in several rounds: its dQ items are the longest, so the
+    backward's one launch starts with them."""
+    cu_k = (0, 130, 230, 360, 490, 520, 584)
+    d = _descs.desc(cu_q=(0, 40, 104), kind=(1, 0), kv_first=(0, 5), kv_count=(5, 1), cu_k=cu_k,
+                    block_index=(0, 1, 2, 3, 4, 0), num_slots=5)
+    run_and_compare(d, 100, hd, torch.bfloat16, 90 + hd)
