@@ -1,9 +1,8 @@
 // Packed whole+shard attention forward in fp32, on the fp32 matrix cores.
 //
 // Same work items and outputs as the bf16 MFMA kernel; every product and sum
-// is fp32 (v_mfma_f32_32x32x2_f32).  A workgroup of 8 waves (two per SIMD)
-// takes 32 query rows of an item, and wave w the 32-key blocks w, w+8, ... of
-// its keys:
+// is fp32 (v_mfma_f32_32x32x2_f32).  A workgroup of NW waves takes 32 query rows
+// of an item, and wave w the 32-key blocks w, w+NW, ... of its keys:
 //   S^T = K Q^T    one query per lane (Q in registers as the B operand), K
 //                  straight from memory as A: a lane's 16-byte load of a key
 //                  row feeds four MFMAs, which fixes the order in which d is
@@ -14,7 +13,7 @@
 //                  16-byte loads of a value row, each feeding the four (two
 //                  for d = 64) d blocks of the output
 // No wave shares a key with another, so nothing is staged in LDS and the loop
-// has no barrier; the eight partial results of a query are combined through
+// has no barrier; the partial results of a query are combined through
 // LDS at the end.
 //
 // Bound: the fp32 matrix rate (4 d FLOP per pair), with 32 query rows so that
@@ -22,7 +21,10 @@
 // one query per lane on the vector ALUs, keys visited one by one (64 threads
 // per workgroup, about one wave per CU for that image).  Measured there (d =
 // 128, 15.0 GFLOP): 3,768 us before, 186 us now (81 TFLOP/s; a plain fp32
-// library GEMM reaches 153), the error against fp64 1.0e-6 before, 4.9e-7 now.
+// library GEMM reaches 153) with NW = 8, one workgroup per CU, and 170 us (88
+// TFLOP/s) with NW = 4, two per CU, which share a CU's matrix cores and so even
+// out its last rounds; the error against fp64 was 1.0e-6 before and is 4.9e-7.
+// Launches of no more tiles than CUs take NW = 8 (152 tiles: 50.7 us, NW = 4 52.7).
 
 #include "zl_device.h"
 #include "zl_internal.h"
@@ -30,8 +32,6 @@
 namespace zl {
 namespace {
 
-constexpr int NW = 8;                // waves per workgroup
-constexpr int NT = 64 * NW;
 constexpr int BM = 32;               // query rows per workgroup
 constexpr int BN = 32;               // keys per block
 constexpr int SUB = kFwd32TileM / BM;  // workgroups per work item
@@ -41,8 +41,8 @@ __device__ __forceinline__ f32x16 mfma32f(float a, float b, const f32x16& c) {
   return __builtin_amdgcn_mfma_f32_32x32x2f32(a, b, c, 0, 0, 0);
 }
 
-template <int D>
-__global__ __launch_bounds__(NT, 1) void fwd_fp32_kernel(FwdParams p) {
+template <int D, int NW>
+__global__ __launch_bounds__(64 * NW, 2) void fwd_fp32_kernel(FwdParams p) {
   constexpr int NC = D / 8;    // 16-byte K loads per block and lane
   constexpr int DB = D / 32;   // output blocks of 32 d
   constexpr int PF = 8;        // loads in flight per wave
@@ -231,15 +231,18 @@ __global__ __launch_bounds__(NT, 1) void fwd_fp32_kernel(FwdParams p) {
 
 }  // namespace
 
-hipError_t launch_fwd_fp32(const FwdParams& p, int head_dim, hipStream_t s) {
+template <int D>
+hipError_t launch_d(const FwdParams& p, hipStream_t s) {
   // The grid's thread count has to stay below 2^32: further tiles are taken in turn.
   const int64_t tiles = (int64_t)p.n_items * SUB;
-  const dim3 grid((unsigned)(tiles < (1 << 20) ? tiles : (1 << 20))), block(NT);
-  if (head_dim == 128)
-    hipLaunchKernelGGL(fwd_fp32_kernel<128>, grid, block, 0, s, p);
-  else
-    hipLaunchKernelGGL(fwd_fp32_kernel<64>, grid, block, 0, s, p);
+  const dim3 grid((unsigned)(tiles < (1 << 20) ? tiles : (1 << 20)));
+  if (tiles > device_cus()) hipLaunchKernelGGL((fwd_fp32_kernel<D, 4>), grid, dim3(256), 0, s, p);
+  else hipLaunchKernelGGL((fwd_fp32_kernel<D, 8>), grid, dim3(512), 0, s, p);
   return hipGetLastError();
+}
+
+hipError_t launch_fwd_fp32(const FwdParams& p, int head_dim, hipStream_t s) {
+  return head_dim == 128 ? launch_d<128>(p, s) : launch_d<64>(p, s);
 }
 
 }  // namespace zl
