@@ -145,8 +145,10 @@ __device__ __forceinline__ void fwd_store(const __attribute__((address_space(4))
   }
 }
 
-template <int D, int PARTS>
-__global__ __launch_bounds__(NT, 1) void fwd_bf16_kernel(FwdParams p) {
+// PER_CU: workgroups per compute unit that the registers leave room for (d = 64
+// with 128 VGPRs: two, and their LDS fits as well).
+template <int D, int PARTS, int PER_CU>
+__global__ __launch_bounds__(NT, PER_CU == 2 ? 4 : 1) void fwd_bf16_kernel(FwdParams p) {
   using Split = KeySplit<PARTS>;
   constexpr int PITCH = Pad<D>::PITCH;
   constexpr int TN = 2 * BN;  // keys per staged tile: two steps per barrier
@@ -561,17 +563,19 @@ __global__ __launch_bounds__(NT, 1) void fwd_bf16_kernel(FwdParams p) {
 
 }  // namespace
 
-template <int D, int PARTS>
+template <int D, int PARTS, int PER_CU = 1>
 hipError_t launch_parts(FwdParams p, hipStream_t s) {
-  const int grid = launch_grid(reinterpret_cast<const void*>(fwd_bf16_kernel<D, PARTS>), NT, p.n_items, p.wq);
+  const int grid = launch_grid(reinterpret_cast<const void*>(fwd_bf16_kernel<D, PARTS, PER_CU>), NT, p.n_items, p.wq);
   if (grid < 0) return hipErrorInvalidValue;
   if (grid == p.n_items) p.wq = nullptr;  // a single round: nothing to claim
-  hipLaunchKernelGGL((fwd_bf16_kernel<D, PARTS>), dim3(grid), dim3(NT), 0, s, p);
+  hipLaunchKernelGGL((fwd_bf16_kernel<D, PARTS, PER_CU>), dim3(grid), dim3(NT), 0, s, p);
   return hipGetLastError();
 }
 
 template <int D>
 hipError_t launch_d(const FwdParams& p, hipStream_t s) {
+  if constexpr (D == 64)
+    if (p.split == 0 && p.many_long) return launch_parts<D, 1, 2>(p, s);
   return p.split == 0 ? launch_parts<D, 1>(p, s) : p.split == 1 ? launch_parts<D, 2>(p, s) : launch_parts<D, 4>(p, s);
 }
 

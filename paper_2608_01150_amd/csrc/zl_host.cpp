@@ -311,6 +311,20 @@ BwdPlan choose_bwd(const std::vector<zl::Item>& kv, const std::vector<zl::Item>&
   return b;
 }
 
+// Whether a forward launch has the items for two workgroups per CU, where the
+// kernel's registers allow them (d = 64): at least four rounds of items with 1536
+// keys on average.  Two share a CU's matrix cores and hide each other's waits
+// (forward, 24 heads: 2 x 8,160 tokens 910 -> 839 us, 16 x 1560 339 -> 319 us), but
+// the last rounds of short items come out uneven (24 x 600 tokens 109 -> 129 us, 16
+// x 448 54 -> 73 us) and fewer items gain little (4,173 + 6 x 1,021 tokens, 984
+// items: 179 -> 181 us).
+bool many_long_items(const std::vector<zl::Item>& items) {
+  if (items.size() < (size_t)4 * zl::device_cus()) return false;
+  int64_t keys = 0;
+  for (const zl::Item& it : items) keys += it.k_len;
+  return keys >= (int64_t)items.size() * 1536;
+}
+
 struct MergeTable {
   std::vector<zl::MergeSeg> segs;
   std::vector<int32_t> slots;
@@ -340,6 +354,7 @@ struct Plan {
   int32_t n_items = 0;          // forward items, or backward dK/dV items
   int32_t n_items2 = 0;         // backward dQ items
   int32_t split = 0;            // how the forward or dQ query tiles are split (bf16, see choose_split)
+  bool many_long = false;       // forward: many_long_items
   bool fused = false;           // backward: dK/dV and dQ items in one launch,
   bool dq_first = false;        // the dQ items first
   int32_t n_segs = 0;
@@ -423,6 +438,7 @@ zl_status build_plan_host(const zl_seg_desc* d, int32_t H, zl_dtype dt, int op, 
     if (items.size() > (size_t)INT32_MAX) return fail(ZL_ERR_UNSUPPORTED, "too many work items");
     p.n_items = (int32_t)items.size();
     if (dt == ZL_BF16) p.split = choose_split(items, zl::kFwdTileM);
+    p.many_long = many_long_items(items);
     p.host.resize(items.size() * sizeof(zl::Item));
     if (!items.empty()) std::memcpy(p.host.data(), items.data(), p.host.size());
   }
@@ -678,6 +694,7 @@ zl_status zl_attn_fwd_ex(const zl_seg_desc* desc, int32_t H, int32_t hd, zl_dtyp
   p.lse_part = lse_part;
   p.items = static_cast<const zl::Item*>(plan->dev);
   p.split = plan->split;
+  p.many_long = plan->many_long ? 1 : 0;
   p.n_items = plan->n_items << p.split;
   p.num_heads = H;
   p.slot_stride = (int64_t)sh.total_q * H * hd;
@@ -725,6 +742,7 @@ zl_status zl_attn_fwd_step(const zl_seg_desc* desc, int32_t H, int32_t hd, zl_dt
   p.lse = lse;
   p.items = static_cast<const zl::Item*>(plan->dev);
   p.split = plan->split;
+  p.many_long = plan->many_long ? 1 : 0;
   p.n_items = plan->n_items << p.split;
   p.num_heads = H;
   p.scale = scale;

@@ -66,6 +66,7 @@ struct FwdParams {
   float scale_log2;      // softmax scale * log2(e)
   int32_t xcd_chunk;
   int32_t split;         // the launch runs n_items = (table items) << split sub-items (see sub_item)
+  int32_t many_long;     // enough long items for two workgroups per CU (d = 64)
   // Ring-step mode (zl_attn_fwd_step): SHARD items fold their block into the
   // running (o_acc, lse_acc) instead of writing a partial slot.
   int32_t step_mode;

@@ -92,3 +92,22 @@ def test_long_dq_items_first(hd):
     d = _descs.desc(cu_q=(0, 40, 104), kind=(1, 0), kv_first=(0, 5), kv_count=(5, 1), cu_k=cu_k,
                     block_index=(0, 1, 2, 3, 4, 0), num_slots=5)
     run_and_compare(d, 100, hd, torch.bfloat16, 90 + hd)
+
+
+def test_two_workgroups_per_cu():
+    """d = 64 with more than four rounds of long items (1040 of 1601 keys): the forward runs two
+    workgroups per compute unit.  64 rows of every head against the oracle."""
+    from tests._gpu import api, to64
+    import numpy as np
+    import oracle
+    n, H, hd = 1601, 149, 64
+    g = torch.Generator().manual_seed(83)
+    q, k, v = (torch.randn((n, H, hd), generator=g).to(torch.bfloat16) for _ in range(3))
+    d = _descs.desc(cu_q=(0, n), kind=(0,), kv_first=(0,), kv_count=(1,), cu_k=(0, n), block_index=(0,), num_slots=0)
+    out, lse, _, _ = api.attn_fwd(api.SegDesc.of(d), q.cuda(), k.cuda(), v.cuda(), hd ** -0.5)
+    rows = np.concatenate([np.arange(0, 48), np.arange(n - 16, n)])
+    out, lse = to64(out), to64(lse)
+    for h in range(H):
+        o, l = oracle.attend(q[rows, h].double().numpy(), k[:, h].double().numpy(), v[:, h].double().numpy(), hd ** -0.5)
+        assert np.abs(out[rows, h] - o).max() <= 2e-2
+        assert np.abs(lse[rows, h] - l).max() <= 1e-3
