@@ -333,14 +333,15 @@ __device__ __forceinline__ int wq_claim(int* ctr, int tries) { return atomicAdd(
 // counters picks the next queue that still holds items: claiming from each in
 // turn made every workgroup wait for up to eight atomics one after another when
 // it ran out of work (3 to 12 us at the end of a launch; two round trips now).
-// A queue whose claim fails stays empty, so the loop ends after at most nine
-// looks.
+// A queue whose claim failed is not tried again, so the loop ends after at most
+// nine looks.
 __device__ __forceinline__ int wq_next(int* ctr, int n, int grid, int chunk, int* tries, int pending) {
   int t = *tries;
   if (t >= 8) return -1;
   const int xcd = xcd_id();
   auto len = [&](int y) { return (n - y + 7) >> 3; };        // positions y + 8k below n
   auto first = [&](int y) { return (grid - y + 7) >> 3; };   // of those, taken by the first round
+  int empty = 0;  // bit i: a claim on queue (xcd + i) % 8 failed
   for (;;) {
     if (pending >= 0) {
       const int y = (xcd + t) & 7, k = first(y) + pending;
@@ -348,6 +349,7 @@ __device__ __forceinline__ int wq_next(int* ctr, int n, int grid, int chunk, int
         *tries = t;
         return dispatch_item(8 * k + y, n, chunk);
       }
+      empty |= 1 << t;
     }
     int c[8];
 #pragma unroll
@@ -355,8 +357,8 @@ __device__ __forceinline__ int wq_next(int* ctr, int n, int grid, int chunk, int
     int mask = 0;  // bit y: queue y still holds items
 #pragma unroll
     for (int y = 0; y < 8; ++y) mask |= (first(y) + c[y] < len(y) ? 1 : 0) << y;
-    mask = (mask | mask << 8) >> xcd;  // bit i: queue (xcd + i) % 8
-    if ((mask & 0xFF) == 0) {
+    mask = ((mask | mask << 8) >> xcd) & 0xFF & ~empty;  // bit i: queue (xcd + i) % 8
+    if (mask == 0) {
       *tries = 8;
       return -1;
     }

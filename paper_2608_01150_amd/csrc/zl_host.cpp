@@ -304,7 +304,8 @@ BwdPlan choose_bwd(const std::vector<zl::Item>& kv, const std::vector<zl::Item>&
     return b;
   }
   b.split = choose_split(q, zl::kDqTileM);
-  b.fused = b.split == 0;
+  // one workgroup per item (no queues) must stay within a grid of 2^32 threads
+  b.fused = b.split == 0 && kv.size() + q.size() <= ((size_t)1 << 22);
   // both lists are in order of decreasing q_len * k_len; MFMA FLOPs per pair are 8 d and 6 d
   if (!kv.empty() && !q.empty())
     b.dq_first = 6. * q[0].q_len * q[0].k_len >= 2. * (8. * kv[0].q_len * kv[0].k_len);
