@@ -498,9 +498,17 @@ __device__ __forceinline__ void dq_items(const BwdParams& p, char* lds, ItemStat
 #pragma unroll
       for (int i = 0; i < 16; ++i) negd[i] = nd;
     }
+    // Zeros made per item: a zero vector held across the items would be spilled
+    // and reloaded by each (280 MB of scratch writes on the mixed image-video
+    // batch; one 1560-token image, forward and backward: 93.9 -> 93.2 us).
+    float zero = 0.f;
+    asm volatile("" : "+v"(zero));
     f32x16 dq[D / 32];
 #pragma unroll
-    for (int db = 0; db < D / 32; ++db) dq[db] = f32x16{};
+    for (int db = 0; db < D / 32; ++db) {
+#pragma unroll
+      for (int i = 0; i < 16; ++i) dq[db][i] = zero;
+    }
     __builtin_amdgcn_s_waitcnt(0);  // prologue loads done (see the forward kernel)
 
     const int k0 = Split::part(wave) * Split::KEYS;  // this wave's first key of a tile
