@@ -320,7 +320,8 @@ zl_status zl_attn_bwd_step(const zl_seg_desc* desc, int32_t num_heads, int32_t h
  * and its D / LSE*log2(e) workspace (8 bytes per query row and head, plus
  * 256-byte alignment) go into one library-owned static device array of
  * ZL_NOALLOC_SCRATCH_BYTES per GPU, held by every GPU the library runs on
- * until the process ends.  The tables are built on the host (and cached there
+ * until the process ends (plus 4 KiB for the halves of a small launch's dQ
+ * tiles, see zl_plan_dump).  The tables are built on the host (and cached there
  * per descriptor) and copied into the array on `stream` by every call.
  * Errors: as zl_attn_bwd, plus ZL_ERR_WORKSPACE (nothing enqueued) when the
  * batch needs more than ZL_NOALLOC_SCRATCH_BYTES.  Every call on a GPU uses
@@ -348,8 +349,8 @@ zl_status zl_attn_bwd_noalloc(const zl_seg_desc* desc, int32_t num_heads, int32_
  * k_start, range) ascending.  Writes min(n, cap) items to `items` (may be
  * NULL when cap is 0) and the total count to *n.  *tile_m / *tile_n (may be
  * NULL) receive the query / key tile sizes of that schedule.  A bf16 forward or
- * dQ launch with so few items that smaller tiles still fit one round on the GPU
- * runs each item's query rows as halves or quarters of tile_m.
+ * dQ launch with so few items that halves of them still fit one round on the GPU
+ * runs each item's query rows as halves (with the same results, bit for bit).
  */
 zl_status zl_plan_dump(const zl_seg_desc* desc, int32_t num_heads, int32_t head_dim, zl_dtype dtype,
                        int32_t op, int32_t* items, size_t cap, size_t* n,

@@ -449,15 +449,12 @@ __device__ __forceinline__ void dq_store(const __attribute__((address_space(4)))
 // boundaries play no part in the backward.  128-key K/V tiles rotate through
 // two LDS buffers, fetched one tile ahead (waves 0-3 load K, 4-7 load V, each
 // fetch's instructions spread over the S/dP MFMAs); a tile is two 64-key
-// steps and one barrier.  Launches with few items run tiles of 128 or 64 rows,
-// as the forward does (one 1560-token image, 12 heads: 54.6 -> 39.1 us); a
-// query's parts are plain sums, added in order at the end.
+// steps and one barrier.
 constexpr int kDqThreads = 512;
 
 // Runs dQ items: item `idx` (-1: none), then claimed ones (see dkdv_items).
-template <int D, int PARTS>
+template <int D>
 __device__ __forceinline__ void dq_items(const BwdParams& p, char* lds, ItemState& st, int& parity, int idx, int grid) {
-  using Split = KeySplit<PARTS>;
   constexpr int BN = kDqTileN;                  // 64 keys per step
   constexpr int TN = 2 * BN;                    // keys per staged tile: two steps per barrier
   constexpr int PITCH = Pad<D>::PITCH;
@@ -473,12 +470,12 @@ __device__ __forceinline__ void dq_items(const BwdParams& p, char* lds, ItemStat
   // Items from the launch's work queues, as in the forward.
   int pending = -1;
   while (idx >= 0) {
-    const Item it = sub_item<PARTS>(p.q_items, idx, kDqTileM);
+    const Item it = p.q_items[idx];
     const int H = p.num_heads;
     const int64_t rs = (int64_t)H * D;
 
     // This lane's query row and its Q, dO fragments (B operands).
-    const int qr = Split::rg(wave) * 32 + ln;
+    const int qr = wave * 32 + ln;
     const bool q_ok = qr < it.q_len;
     const int64_t qrow = (int64_t)(it.q_start + qr) * H + it.head;
     const uint16_t* qg = static_cast<const uint16_t*>(p.q) + qrow * D;
@@ -511,9 +508,8 @@ __device__ __forceinline__ void dq_items(const BwdParams& p, char* lds, ItemStat
     }
     __builtin_amdgcn_s_waitcnt(0);  // prologue loads done (see the forward kernel)
 
-    const int k0 = Split::part(wave) * Split::KEYS;  // this wave's first key of a tile
-    const uint32_t a_off = poff<D>(perm32(ln) + k0, g * 8);
-    const uint32_t t_off = tr_lane_off<D>(lane) + poff<D>(k0, 0);
+    const uint32_t a_off = poff<D>(perm32(ln), g * 8);
+    const uint32_t t_off = tr_lane_off<D>(lane);
 
     // Rows past the segment's keys read zero (the buffer range check).
     const uint16_t* kg = static_cast<const uint16_t*>(p.k) + ((int64_t)it.k_start * H + it.head) * D;
@@ -546,9 +542,7 @@ __device__ __forceinline__ void dq_items(const BwdParams& p, char* lds, ItemStat
     //   S/dP MFMAs of kb 0; S/dP MFMAs of kb 1 with the softmax of kb 0;
     //   dQ MFMAs of kb 0 with the softmax of kb 1; dQ MFMAs of kb 1.
     // A operands come from LDS through a ring of loads issued PF MFMAs ahead.
-    // half: which of the tile's two steps (0 or 1, a literal at the call sites),
-    // or -1 for a wave that runs one step of the tile and issues both halves'
-    // loads in it.
+    // half: which of the tile's two steps (0 or 1, a literal at the call sites).
     auto step = [&](const char* kbuf, const char* vbuf, int half) __attribute__((always_inline)) {
       const char* ka = kbuf + a_off;
       const char* va = vbuf + a_off;
@@ -598,11 +592,7 @@ __device__ __forceinline__ void dq_items(const BwdParams& p, char* lds, ItemStat
           dpc[kb] = mfma32(a, of[kk], kk == 0 ? negd : dpc[kb]);
         else
           sc[kb] = mfma32(a, qf[kk], sc[kb]);
-        if (half >= 0) {
-          if (j % DMA_GAP == 1 && j / DMA_GAP < DMA_PER_STEP) dma.issue_one(next_rsrc[half], next_lds[half], j / DMA_GAP);
-        } else if (j >= 1 && j <= 2 * DMA_PER_STEP) {
-          dma.issue_one(next_rsrc[(j - 1) / DMA_PER_STEP], next_lds[(j - 1) / DMA_PER_STEP], (j - 1) % DMA_PER_STEP);
-        }
+        if (j % DMA_GAP == 1 && j / DMA_GAP < DMA_PER_STEP) dma.issue_one(next_rsrc[half], next_lds[half], j / DMA_GAP);
         // kb 1's MFMAs carry kb 0's softmax: 16 elements over NSD/2 MFMAs.
         if (j >= NSD / 2 && ((j - NSD / 2) % (NSD / 16)) == NSD / 16 - 1) softmax2(0, 2 * ((j - NSD / 2) / (NSD / 16)));
         __builtin_amdgcn_sched_barrier(0);
@@ -626,51 +616,8 @@ __device__ __forceinline__ void dq_items(const BwdParams& p, char* lds, ItemStat
       }
     };
 
-    // One 32-key block, for a wave that shares its rows with three others (see
-    // the forward kernel).
-    auto step32 = [&](const char* kbuf, const char* vbuf) __attribute__((always_inline)) {
-      const char* ka = kbuf + a_off;
-      const char* va = vbuf + a_off;
-      const char* kt_ = kbuf + t_off;
-      constexpr int NSD = 2 * (D / 16), NQ = 2 * (D / 32), PF = 8;
-      auto a_op = [&](int j) {
-        return *reinterpret_cast<const u32x4*>(((j & 1) ? va : ka) + poff<D>(0, (j >> 1) * 16));
-      };
-      u32x4 ring[PF];
-#pragma unroll
-      for (int j = 0; j < PF; ++j) ring[j] = a_op(j);
-      __builtin_amdgcn_sched_barrier(0);
-      f32x16 s = f32x16{}, dp = negd;
-#pragma unroll
-      for (int j = 0; j < NSD; ++j) {
-        const u32x4 a = ring[j % PF];
-        if (j + PF < NSD) ring[j % PF] = a_op(j + PF);
-        if (j & 1)
-          dp = mfma32(a, of[j >> 1], dp);
-        else
-          s = mfma32(a, qf[j >> 1], s);
-        if (j < 2 * DMA_PER_STEP)
-          dma.issue_one(next_rsrc[j / DMA_PER_STEP], next_lds[j / DMA_PER_STEP], j % DMA_PER_STEP);
-        __builtin_amdgcn_sched_barrier(0);
-      }
-      static_assert(2 * DMA_PER_STEP <= NSD, "both halves' loads must fit the block");
-      u32x4 c[NQ], pds[2];
-#pragma unroll
-      for (int m = 0; m < NQ; ++m) c[m] = tr_operand<D>(kt_, 16 * (m & 1), (m >> 1) * 32);
-#pragma unroll
-      for (int i = 0; i < 16; i += 2) {
-        float e[2];
-#pragma unroll
-        for (int u = 0; u < 2; ++u)
-          e[u] = __builtin_amdgcn_fmed3f(fast_exp2(fmaf(s[i + u], p.scale_log2, -lse2)), 0.f, 1.f) * dp[i + u];
-        pds[i >> 3][(i & 7) >> 1] = pack_bf16(e[0], e[1]);
-      }
-#pragma unroll
-      for (int m = 0; m < NQ; ++m) dq[m >> 1] = mfma32(c[m], pds[m & 1], dq[m >> 1]);
-    };
-
     // Waves with no query rows skip the math (see the forward kernel).
-    const bool wave_live = Split::rg(wave) * 32 < it.q_len;
+    const bool wave_live = wave * 32 < it.q_len;
     auto run = [&](const char* kbuf, const char* vbuf, int half) __attribute__((always_inline)) {
       if (wave_live) {
         step(kbuf, vbuf, half);
@@ -683,17 +630,8 @@ __device__ __forceinline__ void dq_items(const BwdParams& p, char* lds, ItemStat
     // forward kernel); keys past the range add zero, so a tile whose second
     // half lies past the range skips that step.
     auto tile = [&](const char* kbuf, const char* vbuf, int kt) __attribute__((always_inline)) {
-      if constexpr (PARTS == 1) {
-        run(kbuf, vbuf, 0);
-        if (kt + BN < it.k_len) run(kbuf + BN * PITCH, vbuf + BN * PITCH, 1);
-      } else if (wave_live && kt + k0 < it.k_len) {
-        if constexpr (PARTS == 2) step(kbuf, vbuf, -1);
-        else step32(kbuf, vbuf);
-      } else {
-#pragma unroll
-        for (int e = 0; e < 2 * DMA_PER_STEP; ++e)
-          dma.issue_one(next_rsrc[e / DMA_PER_STEP], next_lds[e / DMA_PER_STEP], e % DMA_PER_STEP);
-      }
+      run(kbuf, vbuf, 0);
+      if (kt + BN < it.k_len) run(kbuf + BN * PITCH, vbuf + BN * PITCH, 1);
     };
 
     auto claim_ahead = [&]() __attribute__((always_inline)) {
@@ -724,36 +662,7 @@ __device__ __forceinline__ void dq_items(const BwdParams& p, char* lds, ItemStat
     wait_vmem();  // the lookahead loads must land before the LDS is reused
 
     // dq[db][i] is (d = db*32 + 16*(i/8) + 8g + i%8, query qr).
-    if constexpr (PARTS > 1) {
-      // Sum the parts of each query: parts 1.. leave dQ in the tile buffers
-      // (two waves in each), part 0 adds them in order.
-      constexpr int O4 = D / 8;                        // 16-byte pieces of dq per lane
-      constexpr int XCH = O4 * 1024;                   // bytes per wave
-      static_assert(2 * XCH <= TILE, "two waves' results must fit a tile buffer");
-      auto at = [&](int w) { return (w < 2 ? ks0 : w < 4 ? ks1 : vs0) + (w & 1) * XCH; };
-
-      __syncthreads();  // every wave is done with the tiles
-      if (Split::part(wave) > 0) {
-        char* x = at(Split::slot(Split::rg(wave), Split::part(wave)));
-#pragma unroll
-        for (int t = 0; t < O4; ++t)
-          *reinterpret_cast<f32x4*>(x + t * 1024 + lane * 16) =
-              f32x4{dq[t / 4][4 * (t % 4)], dq[t / 4][4 * (t % 4) + 1], dq[t / 4][4 * (t % 4) + 2], dq[t / 4][4 * (t % 4) + 3]};
-      }
-      __syncthreads();
-      if (Split::part(wave) == 0) {
-        for (int q = 1; q < PARTS; ++q) {
-          const char* x = at(Split::slot(Split::rg(wave), q));
-#pragma unroll
-          for (int t = 0; t < O4; ++t) {
-            const f32x4 b = *reinterpret_cast<const f32x4*>(x + t * 1024 + lane * 16);
-#pragma unroll
-            for (int e = 0; e < 4; ++e) dq[t / 4][4 * (t % 4) + e] += b[e];
-          }
-        }
-      }
-    }
-    if (q_ok && Split::part(wave) == 0) dq_store<D>(kernargs<BwdParams>(), it, qrow, g, dq);
+    if (q_ok) dq_store<D>(kernargs<BwdParams>(), it, qrow, g, dq);
     const auto* pk = kernargs<BwdParams>();
     if (tid == 0)
       st.item[parity] = pk->wq_q ? wq_next(pk->wq_q, pk->n_q_items, grid, pk->xcd_chunk, &st.tries, pending) : -1;
@@ -774,20 +683,20 @@ __global__ __launch_bounds__(kDkdvThreads, 1) void bwd_dkdv_kernel(BwdParams p) 
   if (threadIdx.x == 0 && p.wq_kv) wq_finish(p.wq_kv);
 }
 
-template <int D, int PARTS>
+template <int D>
 __global__ __launch_bounds__(kDqThreads, 1) void bwd_dq_kernel(BwdParams p) {
   __shared__ __attribute__((aligned(16))) char lds[kDqLds<D>];
   __shared__ ItemState st;
   int parity = 0;
   if (threadIdx.x == 0) st.tries = 0;
-  dq_items<D, PARTS>(p, lds, st, parity, dispatch_item(blockIdx.x, p.n_q_items, p.xcd_chunk), gridDim.x);
+  dq_items<D>(p, lds, st, parity, dispatch_item(blockIdx.x, p.n_q_items, p.xcd_chunk), gridDim.x);
   if (threadIdx.x == 0 && p.wq_q) wq_finish(p.wq_q);
 }
 
 // Both in one launch: the workgroups run the items of one kind and go on to the
 // other kind as they run out; the first ones start with the first kind, the rest
 // of the grid with the second.  DQ_FIRST says which is first (see choose_bwd).
-template <int D, int PARTS, bool DQ_FIRST>
+template <int D, bool DQ_FIRST>
 __global__ __launch_bounds__(kDkdvThreads, 1) void bwd_fused_kernel(BwdParams p) {
   static_assert(kDkdvThreads == kDqThreads, "one workgroup runs both");
   __shared__ __attribute__((aligned(16))) char lds[kDkdvLds<D> > kDqLds<D> ? kDkdvLds<D> : kDqLds<D>];
@@ -799,7 +708,7 @@ __global__ __launch_bounds__(kDkdvThreads, 1) void bwd_fused_kernel(BwdParams p)
   int second = -1;  // this workgroup's first item of the second kind
   if (b < grid1) {
     const int first = dispatch_item(b, n1, p.xcd_chunk);
-    if constexpr (DQ_FIRST) dq_items<D, PARTS>(p, lds, st, parity, first, grid1);
+    if constexpr (DQ_FIRST) dq_items<D>(p, lds, st, parity, first, grid1);
     else dkdv_items<D>(p, lds, st, parity, first, grid1);
     if (p.wq_q) {
       if (threadIdx.x == 0) {
@@ -814,7 +723,7 @@ __global__ __launch_bounds__(kDkdvThreads, 1) void bwd_fused_kernel(BwdParams p)
     second = dispatch_item(b - grid1, n2, p.xcd_chunk);
   }
   if constexpr (DQ_FIRST) dkdv_items<D>(p, lds, st, parity, second, grid2);
-  else dq_items<D, PARTS>(p, lds, st, parity, second, grid2);
+  else dq_items<D>(p, lds, st, parity, second, grid2);
   if (threadIdx.x == 0 && p.wq_q) wq_finish2(p.wq_kv, p.wq_q);
 }
 
@@ -829,38 +738,29 @@ hipError_t launch_dkdv(BwdParams p, hipStream_t s) {
   return hipGetLastError();
 }
 
-template <int D, int PARTS>
+template <int D>
 hipError_t launch_dq(BwdParams p, hipStream_t s) {
-  const int grid = launch_grid(reinterpret_cast<const void*>(bwd_dq_kernel<D, PARTS>), kDqThreads, p.n_q_items, p.wq_q);
+  const int grid = launch_grid(reinterpret_cast<const void*>(bwd_dq_kernel<D>), kDqThreads, p.n_q_items, p.wq_q);
   if (grid < 0) return hipErrorInvalidValue;
   if (grid == p.n_q_items) p.wq_q = nullptr;  // a single round: nothing to claim
-  hipLaunchKernelGGL((bwd_dq_kernel<D, PARTS>), dim3(grid), dim3(kDqThreads), 0, s, p);
+  hipLaunchKernelGGL(bwd_dq_kernel<D>, dim3(grid), dim3(kDqThreads), 0, s, p);
   return hipGetLastError();
 }
 
-template <int D>
-hipError_t launch_dq_d(const BwdParams& p, hipStream_t s) {
-  return p.split_q == 0 ? launch_dq<D, 1>(p, s) : p.split_q == 1 ? launch_dq<D, 2>(p, s) : launch_dq<D, 4>(p, s);
-}
-
-template <int D, int PARTS, bool DQ_FIRST>
+template <int D, bool DQ_FIRST>
 hipError_t launch_fused(BwdParams p, hipStream_t s) {
   const int n = p.n_kv_items + p.n_q_items;
   const int grid =
-      launch_grid(reinterpret_cast<const void*>(bwd_fused_kernel<D, PARTS, DQ_FIRST>), kDqThreads, n, p.wq_q);
+      launch_grid(reinterpret_cast<const void*>(bwd_fused_kernel<D, DQ_FIRST>), kDqThreads, n, p.wq_q);
   if (grid < 0) return hipErrorInvalidValue;
   if (grid == n) p.wq_kv = p.wq_q = nullptr;  // a single round: nothing to claim
-  hipLaunchKernelGGL((bwd_fused_kernel<D, PARTS, DQ_FIRST>), dim3(grid), dim3(kDqThreads), 0, s, p);
+  hipLaunchKernelGGL((bwd_fused_kernel<D, DQ_FIRST>), dim3(grid), dim3(kDqThreads), 0, s, p);
   return hipGetLastError();
 }
 
-// dQ goes first only in launches of several rounds, which run whole tiles.
 template <int D>
 hipError_t launch_fused_d(const BwdParams& p, hipStream_t s) {
-  if (p.dq_first && p.split_q == 0) return launch_fused<D, 1, true>(p, s);
-  return p.split_q == 0   ? launch_fused<D, 1, false>(p, s)
-         : p.split_q == 1 ? launch_fused<D, 2, false>(p, s)
-                          : launch_fused<D, 4, false>(p, s);
+  return p.dq_first ? launch_fused<D, true>(p, s) : launch_fused<D, false>(p, s);
 }
 
 hipError_t launch_bwd_bf16(const BwdParams& p, int head_dim, int stage, hipStream_t s) {
@@ -880,7 +780,7 @@ hipError_t launch_bwd_bf16(const BwdParams& p, int head_dim, int stage, hipStrea
     return head_dim == 128 ? launch_fused_d<128>(p, s) : launch_fused_d<64>(p, s);
   } else {
     if (p.n_q_items == 0) return hipSuccess;
-    return head_dim == 128 ? launch_dq_d<128>(p, s) : launch_dq_d<64>(p, s);
+    return head_dim == 128 ? launch_dq<128>(p, s) : launch_dq<64>(p, s);
   }
   return hipGetLastError();
 }

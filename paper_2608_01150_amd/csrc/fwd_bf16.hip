@@ -17,11 +17,8 @@
 // load K, waves 4-7 load V, each fetch's instructions spread over the S
 // MFMAs); a tile is two 64-key steps and one barrier.  A staged tile serves
 // 256 queries, so the staging costs half as much per MFMA as with 128-row
-// items.  Launches with few items run tiles of 128 or 64 rows instead, two or
-// four waves sharing each 32 rows (KeySplit in zl_device.h): a tile of 128 keys
-// then takes 3,620 or 2,740 cycles instead of 6,100 (bound by the 64 KB it stages:
-// about 1,450 cycles of load issue and 1,000 of latency), and the parts of a row
-// are combined through LDS at the end.
+// items.  The order in which a query row meets its keys is the same in every
+// launch, so its bits do not depend on what else the launch holds.
 //
 // Epilogue: WHOLE items write the final bf16 output and the LSE; SHARD items
 // write the block-normalised partial (fp32, or bf16 on request) and its LSE
@@ -147,9 +144,8 @@ __device__ __forceinline__ void fwd_store(const __attribute__((address_space(4))
 
 // PER_CU: workgroups per compute unit that the registers leave room for (d = 64
 // with 128 VGPRs: two, and their LDS fits as well).
-template <int D, int PARTS, int PER_CU>
+template <int D, int PER_CU>
 __global__ __launch_bounds__(NT, PER_CU == 2 ? 4 : 1) void fwd_bf16_kernel(FwdParams p) {
-  using Split = KeySplit<PARTS>;
   constexpr int PITCH = Pad<D>::PITCH;
   constexpr int TN = 2 * BN;  // keys per staged tile: two steps per barrier
   constexpr int TILE = TN * PITCH;
@@ -175,14 +171,14 @@ __global__ __launch_bounds__(NT, PER_CU == 2 ? 4 : 1) void fwd_bf16_kernel(FwdPa
   int pending = -1;  // thread 0: claim issued ahead
   int parity = 0;
   for (int idx = dispatch_item(blockIdx.x, p.n_items, p.xcd_chunk);;) {
-    const Item it = sub_item<PARTS>(p.items, idx, kFwdTileM);
+    const Item it = p.items[idx];
     const int64_t rs = (int64_t)p.num_heads * D;  // elements between consecutive tokens
     const uint16_t* qg = static_cast<const uint16_t*>(p.q) + ((int64_t)it.q_start * p.num_heads + it.head) * D;
     const uint16_t* kg = static_cast<const uint16_t*>(p.k) + ((int64_t)it.k_start * p.num_heads + it.head) * D;
     const uint16_t* vg = static_cast<const uint16_t*>(p.v) + ((int64_t)it.k_start * p.num_heads + it.head) * D;
 
-    // Q fragments (B operand): query row rg*32+ln, d = 16*kk + 8*g .. +7.
-    const int qr = Split::rg(wave) * 32 + ln;
+    // Q fragments (B operand): query row wave*32+ln, d = 16*kk + 8*g .. +7.
+    const int qr = wave * 32 + ln;
     const bool q_ok = qr < it.q_len;
     u32x4 qf[D / 16];
 #pragma unroll
@@ -209,9 +205,8 @@ __global__ __launch_bounds__(NT, PER_CU == 2 ? 4 : 1) void fwd_bf16_kernel(FwdPa
     for (int db = 0; db < D / 32; ++db) o[db] = f32x16{};
 
     // Per-lane LDS offsets: A-operand row perm32(ln), transpose piece.
-    const int k0 = Split::part(wave) * Split::KEYS;  // this wave's first key of a tile
-    const uint32_t a_off = poff<D>(perm32(ln) + k0, g * 8);
-    const uint32_t t_off = tr_lane_off<D>(lane) + poff<D>(k0, 0);
+    const uint32_t a_off = poff<D>(perm32(ln), g * 8);
+    const uint32_t t_off = tr_lane_off<D>(lane);
 
     // K/V tile starting at key kt; rows past the range (and whole tiles past
     // it, fetched by the lookahead) read zero and are masked below.  Waves 0-3
@@ -246,9 +241,7 @@ __global__ __launch_bounds__(NT, PER_CU == 2 ? 4 : 1) void fwd_bf16_kernel(FwdPa
     //   S of kb 0;  S of kb 1 with the softmax of kb 0;  check of kb 0;
     //   PV of kb 0 with the exponentials of kb 1;  check of kb 1;  PV of kb 1.
     // A operands come from LDS through rings of loads issued ahead of use.
-    // half: which of the tile's two steps (0 or 1, a literal at the call sites),
-    // or -1 for a wave that runs one step of the tile and issues both halves'
-    // loads in it.
+    // half: which of the tile's two steps (0 or 1, a literal at the call sites).
     auto step = [&](const char* kbuf, const char* vbuf, int kt, int half) __attribute__((always_inline)) {
       const char* ka = kbuf + a_off;
       const char* vt = vbuf + t_off;
@@ -256,7 +249,6 @@ __global__ __launch_bounds__(NT, PER_CU == 2 ? 4 : 1) void fwd_bf16_kernel(FwdPa
       constexpr int NP = 2 * (D / 32) * 2;    // PV MFMAs per step
       constexpr int PF = 6, PFC = 3;
       constexpr int DMA_GAP = NS / DMA_PER_STEP;  // S MFMAs between the spread fetch's instructions
-      static_assert(2 * DMA_PER_STEP < NS, "both halves' loads must fit one step");
       static_assert(DMA_GAP >= 2 && (DMA_PER_STEP - 1) * DMA_GAP + 1 < NS, "spread fetch must fit the S MFMAs");
       // S operand j: keys of block j/(NS/2) (rows perm32), d chunk j%(NS/2).
       auto a_op = [&](int j) {
@@ -331,11 +323,7 @@ __global__ __launch_bounds__(NT, PER_CU == 2 ? 4 : 1) void fwd_bf16_kernel(FwdPa
         if (j + PF < NS) ring[j % PF] = a_op(j + PF);
         const int kb = j / (NS / 2);
         s[kb] = mfma32(a, qf[j % (NS / 2)], s[kb]);
-        if (half >= 0) {
-          if (j % DMA_GAP == 1 && j / DMA_GAP < DMA_PER_STEP) dma.issue_one(next_rsrc[half], next_lds[half], j / DMA_GAP);
-        } else if (j >= 1 && j <= 2 * DMA_PER_STEP) {
-          dma.issue_one(next_rsrc[(j - 1) / DMA_PER_STEP], next_lds[(j - 1) / DMA_PER_STEP], (j - 1) % DMA_PER_STEP);
-        }
+        if (j % DMA_GAP == 1 && j / DMA_GAP < DMA_PER_STEP) dma.issue_one(next_rsrc[half], next_lds[half], j / DMA_GAP);
         // Block 1's MFMAs carry block 0's softmax: the mask of a partial tile
         // first, then the eight exponential pairs spread over the remaining
         // slots.  Each packed word and the block's sum are pinned where they are
@@ -384,75 +372,11 @@ __global__ __launch_bounds__(NT, PER_CU == 2 ? 4 : 1) void fwd_bf16_kernel(FwdPa
       __builtin_amdgcn_s_setprio(0);
     };
 
-    // One 32-key block of the tile (keys kt.. kt+31), for a wave that shares its
-    // rows with three others; both halves' loads of the next tile are issued
-    // under its S MFMAs.
-    auto step32 = [&](const char* kbuf, const char* vbuf, int kt) __attribute__((always_inline)) {
-      const char* ka = kbuf + a_off;
-      const char* vt = vbuf + t_off;
-      constexpr int NS = D / 16, NP = 2 * (D / 32);
-      constexpr int PER = (2 * DMA_PER_STEP + NS - 1) / NS;  // loads issued per S MFMA
-      u32x4 ring[NS];
-#pragma unroll
-      for (int j = 0; j < NS; ++j) ring[j] = *reinterpret_cast<const u32x4*>(ka + poff<D>(0, j * 16));
-      __builtin_amdgcn_sched_barrier(0);
-      f32x16 s = f32x16{};
-#pragma unroll
-      for (int j = 0; j < NS; ++j) {
-        s = mfma32(ring[j], qf[j], s);
-#pragma unroll
-        for (int e = j * PER; e < (j + 1) * PER && e < 2 * DMA_PER_STEP; ++e)
-          dma.issue_one(next_rsrc[e / DMA_PER_STEP], next_lds[e / DMA_PER_STEP], e % DMA_PER_STEP);
-        __builtin_amdgcn_sched_barrier(0);
-      }
-      u32x4 v[NP];
-#pragma unroll
-      for (int m = 0; m < NP; ++m) v[m] = tr_operand<D>(vt, 16 * (m & 1), (m >> 1) * 32);
-      const int nvalid = it.k_len - kt;
-      if (nvalid < 32) {
-#pragma unroll
-        for (int i = 0; i < 16; ++i)
-          if (16 * (i >> 3) + 8 * g + (i & 7) >= nvalid) s[i] = -INFINITY;
-      }
-      u32x4 pw[2];
-      float ls;
-      auto expo = [&]() __attribute__((always_inline)) {
-        float l2[2] = {0.f, 0.f};
-#pragma unroll
-        for (int c = 0; c < 8; ++c) {
-          const float e0 = fast_exp2(fmaf(s[2 * c], p.scale_log2, -m_run));
-          const float e1 = fast_exp2(fmaf(s[2 * c + 1], p.scale_log2, -m_run));
-          l2[c & 1] += e0 + e1;
-          pw[c >> 2][c & 3] = pack_bf16(e0, e1);
-        }
-        ls = l2[0] + l2[1];
-      };
-      expo();
-      if (__any(ls > kSumBound)) {  // see kSumBound
-        float mt = s[0];
-#pragma unroll
-        for (int i = 1; i < 16; ++i) mt = fmaxf(mt, s[i]);
-        const float m_new = fmaxf(m_run, xor32_max(mt) * p.scale_log2);
-        const float alpha = fast_exp2(m_run - m_new);
-        m_run = m_new;
-        l_part *= alpha;
-        racc *= alpha;
-#pragma unroll
-        for (int db = 0; db < D / 32; ++db) o[db] *= alpha;
-        expo();
-      }
-      l_part += ls;
-#pragma unroll
-      for (int m = 0; m < NP; ++m) o[m >> 1] = mfma32(v[m], pw[m & 1], o[m >> 1]);
-      racc = mfma16(rsel, pw[0], racc);
-      racc = mfma16(rsel, pw[1], racc);
-    };
-
     // A wave with no query rows in this item (the ragged last tile of a
     // segment) skips the math and only issues its share of the next tile's
     // loads, which the other waves need; the SIMD's other wave then has the
     // matrix core to itself.
-    const bool wave_live = Split::rg(wave) * 32 < it.q_len;
+    const bool wave_live = wave * 32 < it.q_len;
     auto run = [&](const char* kbuf, const char* vbuf, int kt, int half) __attribute__((always_inline)) {
       if (wave_live) {
         step(kbuf, vbuf, kt, half);
@@ -461,22 +385,12 @@ __global__ __launch_bounds__(NT, PER_CU == 2 ? 4 : 1) void fwd_bf16_kernel(FwdPa
         for (int jj = 0; jj < DMA_PER_STEP; ++jj) dma.issue_one(next_rsrc[half], next_lds[half], jj);
       }
     };
-    // One staged tile of TN keys as two steps (one, or one 32-key block, of a
-    // wave that shares its rows), with no barrier between them;
+    // One staged tile of TN keys as two steps, with no barrier between them;
     // a tile whose second half lies past the range runs only its first step
     // (the loop ends there, so the fetch that step would finish is not needed).
     auto tile = [&](const char* kbuf, const char* vbuf, int kt) __attribute__((always_inline)) {
-      if constexpr (PARTS == 1) {
-        run(kbuf, vbuf, kt, 0);
-        if (kt + BN < it.k_len) run(kbuf + BN * PITCH, vbuf + BN * PITCH, kt + BN, 1);
-      } else if (wave_live && kt + k0 < it.k_len) {
-        if constexpr (PARTS == 2) step(kbuf, vbuf, kt + k0, -1);
-        else step32(kbuf, vbuf, kt + k0);
-      } else {
-#pragma unroll
-        for (int e = 0; e < 2 * DMA_PER_STEP; ++e)
-          dma.issue_one(next_rsrc[e / DMA_PER_STEP], next_lds[e / DMA_PER_STEP], e % DMA_PER_STEP);
-      }
+      run(kbuf, vbuf, kt, 0);
+      if (kt + BN < it.k_len) run(kbuf + BN * PITCH, vbuf + BN * PITCH, kt + BN, 1);
     };
 
     auto claim_ahead = [&]() __attribute__((always_inline)) {
@@ -510,46 +424,7 @@ __global__ __launch_bounds__(NT, PER_CU == 2 ? 4 : 1) void fwd_bf16_kernel(FwdPa
       wait_vmem();  // the lookahead loads must land before the workgroup's LDS is released
     }
 
-    float r_run = racc[0];
-    if constexpr (PARTS > 1) {
-      // Combine the parts of each query: parts 1.. leave (o, m, l, r) in the
-      // tile buffers (two waves in each), part 0 folds them in.
-      constexpr int O4 = D / 8;                        // 16-byte pieces of o per lane
-      constexpr int XCH = O4 * 1024 + 3 * 256;         // bytes per wave
-      static_assert(2 * XCH <= TILE, "two waves' results must fit a tile buffer");
-      auto at = [&](int w) { return (w < 2 ? ks0 : w < 4 ? ks1 : vs0) + (w & 1) * XCH; };
-      __syncthreads();  // every wave is done with the tiles
-      if (Split::part(wave) > 0) {
-        char* x = at(Split::slot(Split::rg(wave), Split::part(wave)));
-#pragma unroll
-        for (int t = 0; t < O4; ++t)
-          *reinterpret_cast<f32x4*>(x + t * 1024 + lane * 16) =
-              f32x4{o[t / 4][4 * (t % 4)], o[t / 4][4 * (t % 4) + 1], o[t / 4][4 * (t % 4) + 2], o[t / 4][4 * (t % 4) + 3]};
-        float* st = reinterpret_cast<float*>(x + O4 * 1024);
-        st[lane] = m_run;
-        st[64 + lane] = l_part;
-        st[128 + lane] = r_run;
-      }
-      __syncthreads();
-      if (Split::part(wave) == 0) {
-        for (int q = 1; q < PARTS; ++q) {
-          const char* x = at(Split::slot(Split::rg(wave), q));
-          const float* st = reinterpret_cast<const float*>(x + O4 * 1024);
-          const float mb = st[lane], m_new = fmaxf(m_run, mb);
-          const float fa = fast_exp2(m_run - m_new), fb = fast_exp2(mb - m_new);
-          m_run = m_new;
-          l_part = l_part * fa + st[64 + lane] * fb;
-          r_run = r_run * fa + st[128 + lane] * fb;
-#pragma unroll
-          for (int t = 0; t < O4; ++t) {
-            const f32x4 b = *reinterpret_cast<const f32x4*>(x + t * 1024 + lane * 16);
-#pragma unroll
-            for (int e = 0; e < 4; ++e) o[t / 4][4 * (t % 4) + e] = o[t / 4][4 * (t % 4) + e] * fa + b[e] * fb;
-          }
-        }
-      }
-    }
-    fwd_store<D>(kernargs<FwdParams>(), it, qr, q_ok && Split::part(wave) == 0, g, o, m_run, l_part, r_run);
+    fwd_store<D>(kernargs<FwdParams>(), it, qr, q_ok, g, o, m_run, l_part, racc[0]);
     const auto* pk = kernargs<FwdParams>();
     if (tid == 0) s_item[parity] = pk->wq ? wq_next(pk->wq, pk->n_items, gridDim.x, pk->xcd_chunk, &s_tries, pending) : -1;
     pending = -1;
@@ -563,20 +438,20 @@ __global__ __launch_bounds__(NT, PER_CU == 2 ? 4 : 1) void fwd_bf16_kernel(FwdPa
 
 }  // namespace
 
-template <int D, int PARTS, int PER_CU = 1>
-hipError_t launch_parts(FwdParams p, hipStream_t s) {
-  const int grid = launch_grid(reinterpret_cast<const void*>(fwd_bf16_kernel<D, PARTS, PER_CU>), NT, p.n_items, p.wq);
+template <int D, int PER_CU>
+hipError_t launch_per_cu(FwdParams p, hipStream_t s) {
+  const int grid = launch_grid(reinterpret_cast<const void*>(fwd_bf16_kernel<D, PER_CU>), NT, p.n_items, p.wq);
   if (grid < 0) return hipErrorInvalidValue;
   if (grid == p.n_items) p.wq = nullptr;  // a single round: nothing to claim
-  hipLaunchKernelGGL((fwd_bf16_kernel<D, PARTS, PER_CU>), dim3(grid), dim3(NT), 0, s, p);
+  hipLaunchKernelGGL((fwd_bf16_kernel<D, PER_CU>), dim3(grid), dim3(NT), 0, s, p);
   return hipGetLastError();
 }
 
 template <int D>
 hipError_t launch_d(const FwdParams& p, hipStream_t s) {
   if constexpr (D == 64)
-    if (p.split == 0 && p.many_long) return launch_parts<D, 1, 2>(p, s);
-  return p.split == 0 ? launch_parts<D, 1>(p, s) : p.split == 1 ? launch_parts<D, 2>(p, s) : launch_parts<D, 4>(p, s);
+    if (p.many_long) return launch_per_cu<D, 2>(p, s);
+  return launch_per_cu<D, 1>(p, s);
 }
 
 hipError_t launch_fwd_bf16(const FwdParams& p, int head_dim, hipStream_t s) {

@@ -15,7 +15,9 @@
 
 namespace {
 
-static __device__ __align__(256) char scratch[ZL_NOALLOC_SCRATCH_BYTES];
+// ZL_NOALLOC_SCRATCH_BYTES for what a batch needs with whole dQ tiles, and room for
+// the additional items of a small launch.
+static __device__ __align__(256) char scratch[ZL_NOALLOC_SCRATCH_BYTES + zl::kHalvesBytes];
 
 constexpr int kMaxDevices = 64;
 std::mutex g_scratch_mu;

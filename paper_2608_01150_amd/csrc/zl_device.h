@@ -260,44 +260,6 @@ __device__ __forceinline__ float lanes_sum(float x) {
   return dpp_add<0x4E>(x);                       // quad_perm [2,3,0,1]
 }
 
-// ------------------------------------------------------------- key split
-// Item idx of a launch whose table items of up to tile_m query rows are split
-// into PARTS sub-items of tile_m / PARTS rows: part idx % PARTS of item
-// idx / PARTS (without rows or keys when the item ends before it).
-template <int PARTS>
-__device__ __forceinline__ Item sub_item(const Item* items, int idx, int tile_m) {
-  if constexpr (PARTS == 1) return items[idx];
-  Item it = items[idx / PARTS];
-  const int m = tile_m / PARTS, q0 = (idx % PARTS) * m;
-  it.q_start += q0;
-  it.q_len = max(min(it.q_len - q0, m), 0);
-  if (it.q_len == 0) it.k_len = 0;
-  return it;
-}
-
-// How the 8 waves of a workgroup share a query tile against keys staged as
-// 128-key tiles, with PARTS waves to each group of 32 query rows (row group rg),
-// each taking 128 / PARTS of a tile's keys:
-//   PARTS 1  256 rows, every wave its own 32 against all keys
-//   PARTS 2  128 rows, two waves each
-//   PARTS 4   64 rows, four waves each
-// Smaller tiles give a launch with few of them more workgroups, each done in
-// about a half or a third of a 256-row tile's time; the parts of a row group are
-// combined at the end of the item.  The live waves sit on different SIMDs (wave
-// w on SIMD w % 4) also when the last row groups are empty.
-template <int PARTS>
-struct KeySplit {
-  static_assert(PARTS == 1 || PARTS == 2 || PARTS == 4, "waves per row group");
-  static constexpr int KEYS = 128 / PARTS;  // keys of a tile per wave
-  static constexpr int LOG2 = PARTS == 1 ? 0 : PARTS == 2 ? 1 : 2;
-  __device__ __forceinline__ static int part(int wave) { return PARTS == 1 ? 0 : PARTS == 2 ? wave >> 2 : wave & 3; }
-  __device__ __forceinline__ static int rg(int wave) {
-    return PARTS == 1 ? wave : PARTS == 2 ? (wave & 3) ^ (wave >> 2 << 1) : wave >> 2;
-  }
-  // Exchange slot (0..5) of part q >= 1 of a row group.
-  __device__ __forceinline__ static int slot(int rg, int q) { return PARTS == 2 ? rg : (q - 1) * 2 + rg; }
-};
-
 // ----------------------------------------------------------- work queues
 // Dynamic distribution of a launch's work items over resident workgroups.
 // The work table in dispatch order (dispatch_item) is split into 8 queues:

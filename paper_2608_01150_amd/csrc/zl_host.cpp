@@ -247,42 +247,38 @@ std::vector<zl::Item> build_items(const zl_seg_desc* d, int32_t H, int op, TileC
   return items;
 }
 
-// How far the query tiles of a bf16 forward or dQ launch are split: 0 runs its
-// items as they are (256 rows), 1 and 2 as halves and quarters (see KeySplit in
-// zl_device.h), each done in about 0.6 and 0.45 of a full tile's time per key
-// (6,100 / 3,620 / 2,740 cycles per 128 keys in the forward).  So they pay where
-// a launch leaves compute units idle and all of the smaller tiles still run in
-// one round; with more rounds the halves' higher total costs as much as a better
-// filled last round gives (one segment, 12 heads, forward and backward, 2 rounds
-// of full tiles against 3 of halves: 5,461 tokens +1%, 6,400 -6%, 8,160 -1.7%;
-// 3 x 1560 tokens, 1 round against 2: +17%).  Measured: one 1560-token image, 12
-// heads, 84 items, as halves: forward 44.7 -> 33.0 us, dQ 54.6 -> 39.1 us; one
-// 448-token image as quarters: forward 16.4 -> 13.0 us.
-size_t sub_items(const std::vector<zl::Item>& items, int tile_m, int split) {
-  const int m = tile_m >> split;
-  size_t n = 0;
+// Whether a bf16 forward or dQ launch runs its query tiles as halves (128 rows),
+// by the launch's size: `items` holds them whole, `others` counts the items that
+// share the launch.  A half leaves one wave per SIMD at work, which takes about
+// 0.6 of the whole tile's time per key, so halves pay where a launch leaves compute
+// units idle and all of them still run in one round; with more rounds their higher
+// total costs as much as a better filled last round gives (sixteen 1560-token
+// images, 12 heads, the last 128 items as halves: forward +1.5%, dQ +1.8%).
+// Quarters gain nothing more, since a half's waves have a SIMD each already.  A
+// row meets its keys in the same order in either tile, so its bits are the same.
+// Measured (12 heads): one 448-token image, forward 16.4 -> 13.2 us; one 1560-token
+// image, forward and backward 104.3 -> 92.0 us; 2500 tokens, forward 61.8 -> 47.2 us.
+size_t launch_slots() { return (size_t)std::min(zl::device_cus(), zl::kMaxHalfItems); }
+
+bool halves_fit(const std::vector<zl::Item>& items, int tile_m, size_t others) {
+  if (items.size() + others > launch_slots()) return false;
+  const int m = tile_m / 2;
+  size_t n = others;
   for (const zl::Item& it : items) n += (size_t)((it.q_len + m - 1) / m);
-  return n;
+  return n <= launch_slots();
 }
 
-int choose_split(const std::vector<zl::Item>& items, int tile_m) {
-  const size_t slots = (size_t)zl::device_cus();
-  if (items.size() > slots) return 0;
-  for (int split = 2; split > 0; --split)
-    if (sub_items(items, tile_m, split) <= slots) return split;
-  return 0;
-}
-
-// The backward's dK/dV and dQ items in one launch or two, and the dQ split.
+// The backward's dK/dV and dQ items in one launch or two.
 // Both need only the preprocess, so one launch lets the workgroups that run out
 // of one kind go on with the other: the chip idles in one last round instead
 // of two, and a small batch runs both side by side.  Measured (forward and
 // backward): one 1560-token image, 12 heads, 156 + 84 items in one round: 109 ->
 // 92 us; 40 heads, 520 + 280 items: 336 -> 290 us; sixteen images, 2,496 + 1,344
 // items: 1,159 -> 1,130 us; the mixed image-video batch, 16,400 + 8,400 items: no
-// difference.  Two launches stay better where the dQ items split into a single
-// round by themselves but the two do not fit one round together (4 x 448 tokens, 12
-// heads, 192 + 96 items: 58.5 us apart with halves, 62.2 in one launch).
+// difference.  Two launches stay better where the dQ items fit a single round as
+// halves but the two kinds together do not (12 heads, 2 x 1000 tokens, 192 + 96
+// items: 82.5 us apart with halves, 90.5 in one launch with halves, 105 with whole
+// tiles; 4 x 448 tokens: 51.1, 57.7 and 59.0 us).
 //
 // In one launch the kind with the longer items goes first, so that the shorter
 // ones even out the end.  dQ items run over a segment's whole key range: with a
@@ -291,21 +287,20 @@ int choose_split(const std::vector<zl::Item>& items, int tile_m) {
 // of 0.12 ms; 3,552 us with dK/dV first, 3,315 with dQ first).  Where the two are
 // within a factor of two the order makes 1 to 2% either way, mostly for dK/dV first.
 struct BwdPlan {
-  int32_t split = 0;
+  bool halves = false;  // dQ items as halves
   bool fused = true, dq_first = false;
 };
 
 BwdPlan choose_bwd(const std::vector<zl::Item>& kv, const std::vector<zl::Item>& q) {
-  const size_t slots = (size_t)zl::device_cus();
   BwdPlan b;
-  if (kv.size() + q.size() <= slots) {
-    for (b.split = 2; b.split > 0; --b.split)
-      if (kv.size() + sub_items(q, zl::kDqTileM, b.split) <= slots) break;
-    return b;
-  }
-  b.split = choose_split(q, zl::kDqTileM);
   // one workgroup per item (no queues) must stay within a grid of 2^32 threads
-  b.fused = b.split == 0 && kv.size() + q.size() <= ((size_t)1 << 22);
+  b.fused = kv.size() + q.size() <= ((size_t)1 << 22);
+  if (halves_fit(q, zl::kDqTileM, kv.size())) {
+    b.halves = true;
+  } else if (kv.size() + q.size() > launch_slots() && halves_fit(q, zl::kDqTileM, 0)) {
+    b.halves = true;
+    b.fused = false;
+  }
   // both lists are in order of decreasing q_len * k_len; MFMA FLOPs per pair are 8 d and 6 d
   if (!kv.empty() && !q.empty())
     b.dq_first = 6. * q[0].q_len * q[0].k_len >= 2. * (8. * kv[0].q_len * kv[0].k_len);
@@ -354,7 +349,6 @@ struct Plan {
   std::vector<char> host;       // host copy (source of the upload)
   int32_t n_items = 0;          // forward items, or backward dK/dV items
   int32_t n_items2 = 0;         // backward dQ items
-  int32_t split = 0;            // how the forward or dQ query tiles are split (bf16, see choose_split)
   bool many_long = false;       // forward: many_long_items
   bool fused = false;           // backward: dK/dV and dQ items in one launch,
   bool dq_first = false;        // the dQ items first
@@ -362,6 +356,7 @@ struct Plan {
   int32_t max_slots = 0;        // merge: largest slot_count
   int64_t n_units = 0;
   size_t slots_offset = 0;      // merge: slot list; backward: dQ items
+  size_t whole_bytes = 0;       // backward: size of the tables with whole dQ tiles
 };
 
 size_t align256(size_t n) { return (n + 255) / 256 * 256; }
@@ -425,10 +420,14 @@ zl_status build_plan_host(const zl_seg_desc* d, int32_t H, zl_dtype dt, int op, 
     p.n_items = (int32_t)kv.size();
     p.n_items2 = (int32_t)qi.size();
     const BwdPlan b = choose_bwd(kv, qi);
-    p.split = b.split;
     p.fused = b.fused;
     p.dq_first = b.dq_first;
     p.slots_offset = align256(kv.size() * sizeof(zl::Item));
+    p.whole_bytes = p.slots_offset + qi.size() * sizeof(zl::Item);
+    if (b.halves) {
+      qi = build_items(d, H, ZL_OP_BWD_DQ, {zl::kDqTileM / 2, zl::kDqTileN}, step);
+      p.n_items2 = (int32_t)qi.size();
+    }
     p.host.assign(p.slots_offset + qi.size() * sizeof(zl::Item), 0);
     if (!kv.empty()) std::memcpy(p.host.data(), kv.data(), kv.size() * sizeof(zl::Item));
     if (!qi.empty()) std::memcpy(p.host.data() + p.slots_offset, qi.data(), qi.size() * sizeof(zl::Item));
@@ -437,8 +436,9 @@ zl_status build_plan_host(const zl_seg_desc* d, int32_t H, zl_dtype dt, int op, 
     const int base_op = step ? ZL_OP_FWD : op;
     std::vector<zl::Item> items = build_items(d, H, base_op, tile_cfg(dt, base_op), step);
     if (items.size() > (size_t)INT32_MAX) return fail(ZL_ERR_UNSUPPORTED, "too many work items");
+    if (dt == ZL_BF16 && halves_fit(items, zl::kFwdTileM, 0))
+      items = build_items(d, H, base_op, {zl::kFwdTileM / 2, zl::kFwdTileN}, step);
     p.n_items = (int32_t)items.size();
-    if (dt == ZL_BF16) p.split = choose_split(items, zl::kFwdTileM);
     p.many_long = many_long_items(items);
     p.host.resize(items.size() * sizeof(zl::Item));
     if (!items.empty()) std::memcpy(p.host.data(), items.data(), p.host.size());
@@ -694,9 +694,8 @@ zl_status zl_attn_fwd_ex(const zl_seg_desc* desc, int32_t H, int32_t hd, zl_dtyp
   p.part_bf16 = part_dt == ZL_BF16 ? 1 : 0;
   p.lse_part = lse_part;
   p.items = static_cast<const zl::Item*>(plan->dev);
-  p.split = plan->split;
   p.many_long = plan->many_long ? 1 : 0;
-  p.n_items = plan->n_items << p.split;
+  p.n_items = plan->n_items;
   p.num_heads = H;
   p.slot_stride = (int64_t)sh.total_q * H * hd;
   p.lse_slot_stride = (int64_t)sh.total_q * H;
@@ -742,9 +741,8 @@ zl_status zl_attn_fwd_step(const zl_seg_desc* desc, int32_t H, int32_t hd, zl_dt
   p.out = out;
   p.lse = lse;
   p.items = static_cast<const zl::Item*>(plan->dev);
-  p.split = plan->split;
   p.many_long = plan->many_long ? 1 : 0;
-  p.n_items = plan->n_items << p.split;
+  p.n_items = plan->n_items;
   p.num_heads = H;
   p.scale = scale;
   p.scale_log2 = scale * 1.4426950408889634f;
@@ -964,8 +962,7 @@ zl_status launch_bwd(const BwdCall& c, const Shape& sh, const Plan& plan, const 
   p.kv_items = reinterpret_cast<const zl::Item*>(base);
   p.n_kv_items = plan.n_items;
   p.q_items = reinterpret_cast<const zl::Item*>(base + plan.slots_offset);
-  p.split_q = plan.split;
-  p.n_q_items = plan.n_items2 << plan.split;
+  p.n_q_items = plan.n_items2;
   p.dq_first = plan.dq_first ? 1 : 0;
   p.num_heads = c.H;
   p.total_q = sh.total_q;
@@ -1023,10 +1020,13 @@ zl_status attn_bwd_scratch(const zl_seg_desc* desc, int32_t H, int32_t hd, zl_dt
   if ((st = get_host_plan(desc, H, hd, dt, ZL_OP_BWD, &hp)) != ZL_OK) return st;
   // layout: [dK/dV items | dQ items] (the plan's host bytes), then the workspace
   const size_t tables = align256(hp->host.size());
-  const size_t need = tables + bwd_workspace_bytes(sh, H);
+  // what fits is a matter of the descriptor alone: halves of dQ tiles, used in small
+  // launches, have room of their own in the array
+  static_assert(zl::kMaxHalfItems / 2 * sizeof(zl::Item) <= zl::kHalvesBytes, "room for the halves");
+  const size_t need = align256(hp->whole_bytes) + bwd_workspace_bytes(sh, H);
   if (need > scratch_bytes)
     return fail(ZL_ERR_WORKSPACE, "this batch needs %zu bytes of scratch (work tables %zu, workspace %zu); the "
-                "static scratch holds %zu", need, tables, need - tables, scratch_bytes);
+                "static scratch holds %zu", need, align256(hp->whole_bytes), bwd_workspace_bytes(sh, H), scratch_bytes);
   void* base = nullptr;
   if ((st = acquire(&base)) != ZL_OK) return st;
   hipStream_t s = static_cast<hipStream_t>(stream);

@@ -35,6 +35,11 @@ constexpr int kBwdTileM = 64;        // queries per dK/dV inner step
 constexpr int kDqTileM = 256;        // dQ kernel: 8 waves x 32 query rows per item
 constexpr int kDqTileN = 64;         // keys per dQ inner step
 
+// Launches of few items may run their query tiles as halves: at most this many, and
+// so at most half as many more than whole ones (32 bytes each).
+constexpr int kMaxHalfItems = 256;
+constexpr size_t kHalvesBytes = kMaxHalfItems / 2 * sizeof(Item);
+
 // Work-item index of workgroup `b`.  Workgroups are dispatched round-robin
 // over the 8 XCDs (b % 8); each run of 8*chunk consecutive workgroups is
 // regrouped so that one XCD takes `chunk` consecutive items (neighbouring
@@ -65,7 +70,6 @@ struct FwdParams {
   float scale;           // softmax scale
   float scale_log2;      // softmax scale * log2(e)
   int32_t xcd_chunk;
-  int32_t split;         // the launch runs n_items = (table items) << split sub-items (see sub_item)
   int32_t many_long;     // enough long items for two workgroups per CU (d = 64)
   // Ring-step mode (zl_attn_fwd_step): SHARD items fold their block into the
   // running (o_acc, lse_acc) instead of writing a partial slot.
@@ -115,8 +119,7 @@ struct BwdParams {
   const Item* kv_items;        // dK/dV items: one key tile against all of its segment's queries
   int32_t n_kv_items;
   const Item* q_items;         // dQ items: one query tile against every key of its segment
-  int32_t n_q_items;           // sub-items: (table items) << split_q
-  int32_t split_q;
+  int32_t n_q_items;
   int32_t dq_first;            // one launch for both: dQ items before dK/dV items
   int32_t num_heads;
   int64_t total_q;             // Tq

@@ -212,3 +212,18 @@ def test_partial_dtype_rules():
     assert st == api.ZL_ERR_UNSUPPORTED and "bf16 partials" in api.last_error()
     st = api._merge_ex(d.ptr(), 2, 64, api.ZL_BF16, FAKE, 9, FAKE, d.num_slots, FAKE, FAKE, None)
     assert st == api.ZL_ERR_INVALID_ARG and "partial dtype" in api.last_error()
+
+
+def test_noalloc_scratch_limit_counts_whole_tiles():
+    """What fits the static scratch is set by the tables with whole dQ tiles: a batch that needs exactly
+    its size passes the check (and stops at the missing GPU), also where the launch runs halves of its 8
+    dQ tiles, and one more dK/dV item per head is refused.  The items are mostly those of SHARDs without
+    query rows: 8 heads x (2 + n) of 32 bytes, 256 for the dQ items, two fp32 [200, 8] arrays."""
+    H, n = 8, 131019
+    assert 32 * H * (2 + n) + 256 + 2 * 200 * H * 4 == 32 << 20
+    for extra, want in ((0, api.ZL_ERR_HIP), (1, api.ZL_ERR_WORKSPACE)):
+        m = n + extra
+        d = api.SegDesc(np.r_[0, np.full(m + 1, 200)], np.r_[0, np.ones(m)], np.arange(m + 1), np.ones(m + 1),
+                        np.r_[0, 200 + np.arange(m + 1)], np.zeros(m + 1), 1)
+        st = api._bwd_noalloc(d.ptr(), H, 64, api.ZL_BF16, 0.125, *(FAKE,) * 9, None)
+        assert st == want, api.last_error()

@@ -1,9 +1,8 @@
-"""Query tiles of 256, 128 and 64 rows (forward and dQ) at their edges against
-the fp64 oracle.  The library picks the tile by the launch's size: few heads
-give tiles of 64 rows (four waves share a row group), tens of heads 128, and
-hundreds of items whole tiles of 256; the backward runs dK/dV and dQ in one
-launch or two.  The oracle's result is the same.
-Bounds as in the other parity tests."""
+"""Launches of few and of many items (forward and backward) at the edges of
+their tiles against the fp64 oracle, and the same segment's results in both: a
+launch's size decides how its items are handed out (one round or queues, dK/dV
+and dQ in one launch or two, one or two workgroups per compute unit), never how
+an item is computed.  Bounds as in the other parity tests."""
 import pytest
 import torch
 
@@ -37,14 +36,13 @@ def test_tile_edges(heads, hd):
 @pytest.mark.parametrize("heads", [2, 20, 30, 160])
 def test_one_long_segment(heads):
     # one segment: 3 tiles of 256 rows, the last one ragged; several 128-key tiles.  The backward's dK/dV
-    # and dQ run in one launch, in a single round with quarters, halves and whole tiles, then in rounds.
+    # and dQ run in one launch, in a single round (2, 20 and 30 heads), then in rounds.
     d = _descs.desc(cu_q=(0, 523), kind=(0,), kv_first=(0,), kv_count=(1,), cu_k=(0, 523), block_index=(0,), num_slots=0)
     run_and_compare(d, heads, 128, torch.bfloat16, 70 + heads)
 
 
 def test_scores_jump_across_parts():
-    """Keys that beat the running maximum far beyond the fast path's bound, each time in another wave's
-    share of the keys: the parts are combined at different maxima."""
+    """Keys that beat the running maximum far beyond the fast path's bound, each in another 32-key block."""
     from tests._gpu import api, to64
     import numpy as np
     import oracle
@@ -111,3 +109,24 @@ def test_two_workgroups_per_cu():
         o, l = oracle.attend(q[rows, h].double().numpy(), k[:, h].double().numpy(), v[:, h].double().numpy(), hd ** -0.5)
         assert np.abs(out[rows, h] - o).max() <= 2e-2
         assert np.abs(lse[rows, h] - l).max() <= 1e-3
+
+
+@pytest.mark.parametrize("hd", [64, 128])
+@pytest.mark.parametrize("n,others", [(448, 12), (300, 40), (1601, 14)])
+def test_bits_do_not_depend_on_the_launch(n, others, hd):
+    """A segment alone (its items fit one round with compute units to spare) and among `others` more of
+    its length (several rounds): the same outputs and gradients, bit for bit."""
+    from tests._gpu import api
+    H, scale = 12, hd ** -0.5
+    g = torch.Generator(device="cuda").manual_seed(84)
+    q, k, v, do = (torch.randn((n * (1 + others), H, hd), generator=g, device="cuda").to(torch.bfloat16) for _ in range(4))
+    res = []
+    for m in (1 + others, 1):
+        cu = tuple(n * i for i in range(m + 1))
+        desc = api.SegDesc.of(_descs.desc(cu_q=cu, kind=(0,) * m, kv_first=tuple(range(m)), kv_count=(1,) * m, cu_k=cu,
+                                          block_index=(0,) * m, num_slots=0))
+        t = [x[:n * m] for x in (q, k, v, do)]
+        out, lse, _, _ = api.attn_fwd(desc, *t[:3], scale)
+        res.append((out, lse) + tuple(api.attn_bwd(desc, *t[:3], out, lse, t[3], scale)))
+    for name, many, one in zip(("out", "lse", "dq", "dk", "dv"), *res):
+        assert torch.equal(many[:n], one), name

@@ -238,12 +238,13 @@ def test_segment_isolation_and_determinism():
     assert not torch.equal(a[0][200:277], c[0][200:277])
 
 
-def test_ring_step_mode_equals_all_blocks_mode():
+@pytest.mark.parametrize("H", [2, 40])   # 40: the all-blocks launch has 240 items, a block's 80
+def test_ring_step_mode_equals_all_blocks_mode(H):
     """A shard against all of its blocks in one launch gives the same partials,
     bit for bit, as one launch per block (the ring's per-step call)."""
     d = _descs.desc(cu_q=(0, 300), kind=(1,), kv_first=(0,), kv_count=(3,),
                     cu_k=(0, 200, 456, 500), block_index=(2, 0, 1), num_slots=3)
-    H, hd = 2, 128
+    hd = 128
     q, k, v, _ = _inputs(d, H, hd, torch.bfloat16, 4)
     qd, kd_, vd = q.cuda(), k.cuda(), v.cuda()
     _, _, o_all, l_all = api.attn_fwd(api.SegDesc.of(d), qd, kd_, vd, 0.09)

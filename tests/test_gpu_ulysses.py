@@ -71,5 +71,10 @@ def test_ulysses_group2_d64():
     _run(G=2, H=6, hd=64, shard_lens=((128, 33), (129, 32)), seed=42)
 
 
+def test_ulysses_group8_many_heads():
+    # all heads in one launch: 320 items; a rank's 20 heads: 40
+    _run(G=8, H=160, hd=128, shard_lens=((38,), (37,), (38,), (37,), (38,), (37,), (38,), (37,)), seed=44)
+
+
 def test_ulysses_group1_is_identity_layout():
     _run(G=1, H=4, hd=128, shard_lens=((100, 7),), seed=43)
