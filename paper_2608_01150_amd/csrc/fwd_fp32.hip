@@ -1,7 +1,7 @@
 // Packed whole+shard attention forward in fp32, on the fp32 matrix cores.
 //
 // Same work items and outputs as the bf16 MFMA kernel; every product and sum
-// is fp32 (v_mfma_f32_32x32x2_f32).  A workgroup of NW waves takes 32 query rows
+// is fp32 (v_mfma_f32_32x32x2_f32).  A workgroup of NW = 4 waves takes 32 query rows
 // of an item, and wave w the 32-key blocks w, w+NW, ... of its keys:
 //   S^T = K Q^T    one query per lane (Q in registers as the B operand), K
 //                  straight from memory as A: a lane's 16-byte load of a key
@@ -20,11 +20,12 @@
 // a 1560-token image of 12 heads (588 tiles) fills the 256 CUs.  It replaces
 // one query per lane on the vector ALUs, keys visited one by one (64 threads
 // per workgroup, about one wave per CU for that image).  Measured there (d =
-// 128, 15.0 GFLOP): 3,768 us before, 186 us now (81 TFLOP/s; a plain fp32
-// library GEMM reaches 153) with NW = 8, one workgroup per CU, and 170 us (88
-// TFLOP/s) with NW = 4, two per CU, which share a CU's matrix cores and so even
-// out its last rounds; the error against fp64 was 1.0e-6 before and is 4.9e-7.
-// Launches of no more tiles than CUs take NW = 8 (152 tiles: 50.7 us, NW = 4 52.7).
+// 128, 15.0 GFLOP): 3,768 us before, 170 us now (88 TFLOP/s; a plain fp32
+// library GEMM reaches 153), two workgroups per CU, which share a CU's matrix
+// cores and so even out its last rounds; the error against fp64 was 1.0e-6 before
+// and is 4.9e-7.  NW = 8 (one workgroup per CU) takes 186 us, and 50.7 instead of
+// 52.7 us for 152 tiles; NW decides which keys a wave sums, so it is the same in every
+// launch: a segment's bits do not depend on what else the launch holds.
 
 #include "zl_device.h"
 #include "zl_internal.h"
@@ -34,6 +35,7 @@ namespace {
 
 constexpr int BM = 32;               // query rows per workgroup
 constexpr int BN = 32;               // keys per block
+constexpr int NW = 4;                // waves per workgroup
 constexpr int SUB = kFwd32TileM / BM;  // workgroups per work item
 static_assert(kFwd32TileM % BM == 0 && kFwd32TileN == BN, "tile shapes");
 
@@ -41,7 +43,7 @@ __device__ __forceinline__ f32x16 mfma32f(float a, float b, const f32x16& c) {
   return __builtin_amdgcn_mfma_f32_32x32x2f32(a, b, c, 0, 0, 0);
 }
 
-template <int D, int NW>
+template <int D>
 __global__ __launch_bounds__(64 * NW, 2) void fwd_fp32_kernel(FwdParams p) {
   constexpr int NC = D / 8;    // 16-byte K loads per block and lane
   constexpr int DB = D / 32;   // output blocks of 32 d
@@ -236,8 +238,7 @@ hipError_t launch_d(const FwdParams& p, hipStream_t s) {
   // The grid's thread count has to stay below 2^32: further tiles are taken in turn.
   const int64_t tiles = (int64_t)p.n_items * SUB;
   const dim3 grid((unsigned)(tiles < (1 << 20) ? tiles : (1 << 20)));
-  if (tiles > device_cus()) hipLaunchKernelGGL((fwd_fp32_kernel<D, 4>), grid, dim3(256), 0, s, p);
-  else hipLaunchKernelGGL((fwd_fp32_kernel<D, 8>), grid, dim3(512), 0, s, p);
+  hipLaunchKernelGGL(fwd_fp32_kernel<D>, grid, dim3(64 * NW), 0, s, p);
   return hipGetLastError();
 }
 
