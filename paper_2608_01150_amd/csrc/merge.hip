@@ -4,9 +4,9 @@
 // A unit is one (shard row, head).  D/4 (fp32 partials) or D/8 (bf16)
 // consecutive lanes own a unit, each holding 4 or 8 consecutive values of the
 // row, so every slot's partial row is read with one fully coalesced 16-byte
-// load per lane.  Slots are taken
-// in passes of PASS slots whose loads are all issued before any is used, combined
-// online across passes (running maximum and sum).  The kernel is HBM-bound:
+// load per lane.  Slots are combined
+// online in groups of 8 (running maximum and sum), a group's partials loaded PASS
+// at a time; the grouping does not depend on PASS, so neither do the results.  The kernel is HBM-bound:
 // per unit it reads S*(4d+4) bytes (S*(2d+4) with bf16 partials, one 8-byte
 // load per lane and slot) and writes 2d+4 (bf16) or 4d+4 bytes; the bf16 output
 // is stored non-temporally (8 fp32 slots of 9,450 rows, 40 heads: 284 -> 271 us,
@@ -19,6 +19,8 @@ namespace zl {
 namespace {
 
 constexpr int NT = 256;
+constexpr int kGroup = 8;  // slots that share one update of the running maximum
+
 template <int D, bool OUT_BF16, bool PART_BF16, int PASS>
 __global__ __launch_bounds__(NT) void merge_kernel(MergeParams p) {
   // A lane holds E consecutive values of the row: 4 fp32 or 8 bf16 partial
@@ -40,45 +42,55 @@ __global__ __launch_bounds__(NT) void merge_kernel(MergeParams p) {
   const int64_t row = (int64_t)sg.row_start * p.num_heads + (u - sg.unit_start);  // token*H + head
   const int32_t* slots = p.slots + sg.slot_first;
 
-  // Online combine over passes of up to 8 slots: every pass issues all of its
-  // LSE and partial loads before using any.  m is the running maximum, l the
-  // running sum of exp(LSE_b - m), acc the running sum of exp(LSE_b - m) O_b.
+  // Online combine over groups of up to 8 slots: a group issues all of its LSE
+  // loads and those of its first PASS partials before using any.  m is the running
+  // maximum, l the running sum of exp(LSE_b - m), acc the running sum of
+  // exp(LSE_b - m) O_b.
   float m = -INFINITY, l = 0.f;
   float acc[E];
 #pragma unroll
   for (int t = 0; t < E; ++t) acc[t] = 0.f;
-  for (int b0 = 0; b0 < sg.slot_count; b0 += PASS) {
-    const int nb = min(PASS, sg.slot_count - b0);
-    float lb[PASS];
+  auto load_o = [&](int64_t sl) __attribute__((always_inline)) {
+    const char* src = static_cast<const char*>(p.o_part) + (sl * p.slot_stride + row * D) * (PART_BF16 ? 2 : 4);
+    return __builtin_nontemporal_load(reinterpret_cast<const u32x4*>(src) + sub);
+  };
+  for (int b0 = 0; b0 < sg.slot_count; b0 += kGroup) {
+    const int nb = min(kGroup, sg.slot_count - b0);
+    float lb[kGroup];
+    int32_t sl[kGroup];
     u32x4 ob[PASS];
 #pragma unroll
-    for (int b = 0; b < PASS; ++b) {
+    for (int b = 0; b < kGroup; ++b) {
       lb[b] = -INFINITY;
-      ob[b] = u32x4{0u, 0u, 0u, 0u};
+      if (b < PASS) ob[b] = u32x4{0u, 0u, 0u, 0u};
       if (b < nb) {
-        const int64_t sl = slots[b0 + b];
-        lb[b] = p.lse_part[sl * p.lse_slot_stride + row];
-        const char* src = static_cast<const char*>(p.o_part) + (sl * p.slot_stride + row * D) * (PART_BF16 ? 2 : 4);
-        ob[b] = __builtin_nontemporal_load(reinterpret_cast<const u32x4*>(src) + sub);
+        sl[b] = slots[b0 + b];
+        lb[b] = p.lse_part[sl[b] * p.lse_slot_stride + row];
+        if (b < PASS) ob[b] = load_o(sl[b]);
       }
     }
     float mb = lb[0];
 #pragma unroll
-    for (int b = 1; b < PASS; ++b) mb = fmaxf(mb, lb[b]);
-    if (mb == -INFINITY) continue;  // every slot of this pass is empty
+    for (int b = 1; b < kGroup; ++b) mb = fmaxf(mb, lb[b]);
+    if (mb == -INFINITY) continue;  // every slot of this group is empty
     const float mn = fmaxf(m, mb);
     const float r = expf(m - mn);   // 0 while m is still -inf
     l *= r;
 #pragma unroll
     for (int t = 0; t < E; ++t) acc[t] *= r;
 #pragma unroll
-    for (int b = 0; b < PASS; ++b) {
+    for (int b = 0; b < kGroup; ++b) {
+      if (b > 0 && b % PASS == 0) {
+        if (b >= nb) break;
+#pragma unroll
+        for (int i = 0; i < PASS; ++i) ob[i] = b + i < nb ? load_o(sl[b + i]) : u32x4{0u, 0u, 0u, 0u};
+      }
       const float w = expf(lb[b] - mn);  // 0 for empty slots
       l += w;
 #pragma unroll
       for (int t = 0; t < E; ++t) {
-        const float x = PART_BF16 ? ((t & 1) ? bf16_hi(ob[b][t >> 1]) : bf16_lo(ob[b][t >> 1]))
-                                  : __uint_as_float(ob[b][t]);
+        const u32x4& o = ob[b % PASS];
+        const float x = PART_BF16 ? ((t & 1) ? bf16_hi(o[t >> 1]) : bf16_lo(o[t >> 1])) : __uint_as_float(o[t]);
         acc[t] = fmaf(w, x, acc[t]);
       }
     }
@@ -105,11 +117,11 @@ __global__ __launch_bounds__(NT) void merge_kernel(MergeParams p) {
 
 }  // namespace
 
-// Slots per pass: 8 where one pass then holds every slot (fp32, 8 slots, 9,450
+// Partials per pass: 8 where one pass then holds every slot (fp32, 8 slots, 9,450
 // rows of 40 heads: 267 us, 4 per pass 268), and for more fp32 slots (16 slots:
 // 129.4 against 129.8).  Otherwise 4, whose fewer registers leave more waves in
-// flight: 3 fp32 slots 17.5 -> 16.8 us, 16 bf16 slots 128.8 -> 111.4 us (8 bf16
-// slots 18.2 with 8 per pass, 18.6 with 4).
+// flight: 3 fp32 slots of 4,095 rows and 12 heads 19.3 -> 17.7 us, 16 bf16 slots 46.1
+// -> 38.7 us (8 bf16 slots 18.2 with 8 per pass, 18.6 with 4).
 template <int D, bool OUT_BF16, bool PART_BF16>
 void launch_merge_p(const MergeParams& p, dim3 grid, dim3 block, hipStream_t s) {
   if (p.max_slots <= 4 || (PART_BF16 && p.max_slots > 8))

@@ -37,3 +37,24 @@ def test_slot_counts(slots, part, out_dt, hd):
         fin = np.isfinite(rl)
         np.testing.assert_allclose(gl[fin], rl[fin], rtol=0, atol=1e-5)
         np.testing.assert_allclose(to64(out)[:, h], ro, rtol=2.0 ** -8 if out_dt == torch.bfloat16 else 0, atol=1e-5)
+
+
+@pytest.mark.parametrize("part", [torch.float32, torch.bfloat16])
+def test_bits_do_not_depend_on_the_launch(part):
+    """A shard of 6 slots beside one of 16 (which sets how many partials a pass loads) and by itself."""
+    n, H, hd = 37, 3, 128
+    g = torch.Generator(device="cuda").manual_seed(86)
+    o = torch.randn((16, 2 * n, H, hd), generator=g, device="cuda").to(part)
+    lse = 3 * torch.randn((16, 2 * n, H), generator=g, device="cuda")
+    two = _descs.desc(cu_q=(0, n, 2 * n), kind=(1, 1), kv_first=(0, 6), kv_count=(6, 16), cu_k=tuple(range(23)),
+                      block_index=tuple(range(6)) + tuple(range(16)), num_slots=16)
+    one = _descs.desc(cu_q=(0, n), kind=(1,), kv_first=(0,), kv_count=(6,), cu_k=tuple(range(7)),
+                      block_index=tuple(range(6)), num_slots=16)
+    res = []
+    for d, rows in ((two, 2 * n), (one, n)):
+        out = torch.empty((rows, H, hd), dtype=torch.float32, device="cuda")
+        got = torch.empty((rows, H), device="cuda")
+        api.lse_merge(api.SegDesc.of(d), o[:, :rows].contiguous(), lse[:, :rows].contiguous(), out, got)
+        res.append((out, got))
+    for a, b in zip(*res):
+        assert torch.equal(a[:n], b)
