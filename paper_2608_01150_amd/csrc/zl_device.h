@@ -245,19 +245,25 @@ __device__ __forceinline__ float xor32_sum(float v) {
 }
 
 // Sum over each group of N (8 or 16) consecutive lanes, in every lane of it, by
-// DPP moves (no LDS): mirrors of 16 and 8 lanes pair up lanes whose sums are
-// equal afterwards, then the four of a quad are added.
+// DPP moves (no LDS).  The order is that of a butterfly: lane i with i^8 (N = 16),
+// then i^4, i^2, i^1.  A rotation by 8 of the 16 lanes is i^8, one by 4 is i^4 once
+// lanes 8 apart hold the same sum; with N = 8, i^4 is the mirror of 8 (i^7) and then
+// of 4 (i^3).
 template <int CTRL>
-__device__ __forceinline__ float dpp_add(float x) {
-  return x + __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(x), CTRL, 0xF, 0xF, true));
+__device__ __forceinline__ float dpp_move(float x) {
+  return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(x), CTRL, 0xF, 0xF, true));
 }
 template <int N>
 __device__ __forceinline__ float lanes_sum(float x) {
   static_assert(N == 8 || N == 16, "lanes per group");
-  if constexpr (N == 16) x = dpp_add<0x140>(x);  // row_mirror
-  x = dpp_add<0x141>(x);                         // row_half_mirror
-  x = dpp_add<0xB1>(x);                          // quad_perm [1,0,3,2]
-  return dpp_add<0x4E>(x);                       // quad_perm [2,3,0,1]
+  if constexpr (N == 16) {
+    x += dpp_move<0x128>(x);                  // row_ror:8
+    x += dpp_move<0x124>(x);                  // row_ror:4
+  } else {
+    x += dpp_move<0x1B>(dpp_move<0x141>(x));  // row_half_mirror, quad_perm [3,2,1,0]
+  }
+  x += dpp_move<0x4E>(x);                     // quad_perm [2,3,0,1]
+  return x + dpp_move<0xB1>(x);               // quad_perm [1,0,3,2]
 }
 
 // ----------------------------------------------------------- work queues

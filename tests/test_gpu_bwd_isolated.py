@@ -134,3 +134,29 @@ def test_backward_alone_scaled_video_full_size():
     kidx = torch.as_tensor(k0 + keys, device=dev)
     _check(to64(dk[kidx, h]), gk, f"video head {h} dk")
     _check(to64(dv[kidx, h]), gv, f"video head {h} dv")
+
+
+@pytest.mark.parametrize("hd", [64, 128])
+def test_preprocess_sums_a_row_in_a_fixed_order(hd):
+    """D of a row: each lane's eight products, then the hd/8 lanes as a butterfly (i with i + hd/16, then half
+    of that, down to neighbours).  One product per lane of very different magnitudes makes every order of the
+    lanes round differently; the workspace starts with -D."""
+    n, H = 513, 3
+    lanes = hd // 8
+    rng = np.random.default_rng(64 + hd)
+    s = (rng.choice([-1.0, 1.0], (n, H, lanes)) * 2.0 ** rng.integers(-14, 15, (n, H, lanes))
+         * (1 + rng.integers(0, 128, (n, H, lanes)) / 128)).astype(np.float32)  # exact in bf16
+    o, do = (torch.zeros((n, H, hd), dtype=torch.bfloat16) for _ in range(2))
+    o[:, :, ::8] = 1
+    do[:, :, ::8] = torch.from_numpy(s).to(torch.bfloat16)
+    want = s
+    while want.shape[-1] > 1:
+        half = want.shape[-1] // 2
+        want = want[..., :half] + want[..., half:]
+    desc = api.SegDesc(np.array([0, n]), [0], [0], [1], np.array([0, n]), [0], 0)
+    q, k, v = (torch.zeros((n, H, hd), dtype=torch.bfloat16, device="cuda") for _ in range(3))
+    lse = torch.full((n, H), float(np.log(n)), device="cuda")
+    ws = torch.empty(api.workspace_size(desc, H, hd, torch.bfloat16, api.ZL_OP_BWD), dtype=torch.uint8, device="cuda")
+    api.attn_bwd(desc, q, k, v, o.cuda(), lse, do.cuda(), hd ** -0.5, workspace=ws)
+    got = ws[:4 * n * H].view(torch.float32).view(n, H).cpu().numpy()
+    assert np.array_equal(got, -want[..., 0])
