@@ -2,11 +2,7 @@
 // coalesced QKV-packed all-to-all of Sec. IV-D): layout kernels that surround
 // one block-diagonal attention call on a head subset.  Every kernel moves
 // 16-byte chunks of a head's d-vector, with the destination written in order
-// (coalesced); they are HBM-bound and do no arithmetic.  One chunk per lane,
-// non-temporal on both sides: a plain copy of 201 MB measured 5.94 TB/s with
-// cached accesses and 6.44 with non-temporal ones (two, four and eight chunks per
-// lane 6.2, 6.1 and 4.2), and the four kernels of a 52,440-token group of eight
-// (40 heads, 1.07 GB) 196 -> 177 us.
+// (coalesced); they are HBM-bound and do no arithmetic.  One chunk per lane.
 //
 // Layouts (Hl = H / group heads per rank, rows in sequence order):
 //   local   q, k, v, out_local   [T_local, H, d]
@@ -24,12 +20,15 @@ namespace {
 
 constexpr int NT = 256;
 
+template <bool STREAM>
 __device__ __forceinline__ void move16(const uint16_t* src, uint16_t* dst) {
-  __builtin_nontemporal_store(__builtin_nontemporal_load(reinterpret_cast<const u32x4*>(src)),
-                              reinterpret_cast<u32x4*>(dst));
+  const u32x4* from = reinterpret_cast<const u32x4*>(src);
+  u32x4* to = reinterpret_cast<u32x4*>(dst);
+  if constexpr (STREAM) __builtin_nontemporal_store(__builtin_nontemporal_load(from), to);
+  else *to = *from;
 }
 
-template <int D>
+template <int D, bool STREAM>
 __global__ __launch_bounds__(NT) void pack_qkv_kernel(UlyssesParams p) {
   constexpr int C = D / 8;  // 16-byte chunks per head vector
   const int64_t u = (int64_t)blockIdx.x * NT + threadIdx.x;
@@ -45,10 +44,10 @@ __global__ __launch_bounds__(NT) void pack_qkv_kernel(UlyssesParams p) {
   const int j = (int)(r / p.rows);
   const uint16_t* src = static_cast<const uint16_t*>(which == 0 ? p.a : which == 1 ? p.b : p.c) +
                         (t * p.heads + (int64_t)j * p.heads_local + hh) * D + c * 8;
-  move16(src, static_cast<uint16_t*>(p.dst) + u * 8);
+  move16<STREAM>(src, static_cast<uint16_t*>(p.dst) + u * 8);
 }
 
-template <int D>
+template <int D, bool STREAM>
 __global__ __launch_bounds__(NT) void unpack_qkv_kernel(UlyssesParams p) {
   constexpr int C = D / 8;
   // one thread per (full-layout destination chunk), reading the rank-major source
@@ -63,10 +62,10 @@ __global__ __launch_bounds__(NT) void unpack_qkv_kernel(UlyssesParams p) {
   const int64_t row = r / p.heads_local;  // rank-major row
   const int64_t full = p.row_map[row];
   uint16_t* dst = static_cast<uint16_t*>(which == 0 ? p.dst : which == 1 ? p.dst2 : p.dst3);
-  move16(static_cast<const uint16_t*>(p.a) + u * 8, dst + (full * p.heads_local + hh) * D + c * 8);
+  move16<STREAM>(static_cast<const uint16_t*>(p.a) + u * 8, dst + (full * p.heads_local + hh) * D + c * 8);
 }
 
-template <int D>
+template <int D, bool STREAM>
 __global__ __launch_bounds__(NT) void pack_out_kernel(UlyssesParams p) {
   constexpr int C = D / 8;
   const int64_t u = (int64_t)blockIdx.x * NT + threadIdx.x;
@@ -78,10 +77,10 @@ __global__ __launch_bounds__(NT) void pack_out_kernel(UlyssesParams p) {
   const int64_t row = r / p.heads_local;
   const int64_t full = p.row_map[row];
   const uint16_t* src = static_cast<const uint16_t*>(p.a) + (full * p.heads_local + hh) * D + c * 8;
-  move16(src, static_cast<uint16_t*>(p.dst) + u * 8);
+  move16<STREAM>(src, static_cast<uint16_t*>(p.dst) + u * 8);
 }
 
-template <int D>
+template <int D, bool STREAM>
 __global__ __launch_bounds__(NT) void unpack_out_kernel(UlyssesParams p) {
   constexpr int C = D / 8;
   const int64_t u = (int64_t)blockIdx.x * NT + threadIdx.x;
@@ -93,7 +92,7 @@ __global__ __launch_bounds__(NT) void unpack_out_kernel(UlyssesParams p) {
   const int64_t t = r / p.heads;
   const int j = hd / p.heads_local, hh = hd % p.heads_local;
   const uint16_t* src = static_cast<const uint16_t*>(p.a) + (((int64_t)j * p.rows + t) * p.heads_local + hh) * D + c * 8;
-  move16(src, static_cast<uint16_t*>(p.dst) + u * 8);
+  move16<STREAM>(src, static_cast<uint16_t*>(p.dst) + u * 8);
 }
 
 }  // namespace
@@ -109,9 +108,23 @@ hipError_t launch_ulysses(const UlyssesParams& p, int op, int head_dim, hipStrea
   }
   if (units == 0) return hipSuccess;
   const dim3 grid((unsigned)((units + NT - 1) / NT)), block(NT);
-#define ZL_LAUNCH(KERN)                                                   \
-  if (head_dim == 128) hipLaunchKernelGGL(KERN<128>, grid, block, 0, s, p); \
-  else hipLaunchKernelGGL(KERN<64>, grid, block, 0, s, p);
+  // Non-temporal on both sides where a call reads and writes more than 96 MiB: a copy
+  // of 201 MB ran at 6.44 TB/s against 5.94 with cached accesses, the four calls of a
+  // 52,440-token group of eight (40 heads, 403 MB in the largest call) at 177 us against
+  // 194, of a 28,672-token group of four (12 heads, 132 MB) at 64 against 72.  Below that
+  // the next step finds the data in the 256 MB last-level cache: staging and attention of
+  // a group of eight, 40 heads, 4 x 1560 tokens (48 MB) 67.8 us cached and 72.9
+  // non-temporal, 8 x 1560 (96 MB) 131.6 and 134.4, the staging alone the same either
+  // way; from 4 x 3600 (111 MB) on the staging alone is slower cached (56.7 and 56.0).
+  const bool stream = units * 32 > (int64_t)96 << 20;
+#define ZL_LAUNCH(KERN)                                                                          \
+  if (head_dim == 128) {                                                                         \
+    if (stream) hipLaunchKernelGGL((KERN<128, true>), grid, block, 0, s, p);                      \
+    else hipLaunchKernelGGL((KERN<128, false>), grid, block, 0, s, p);                            \
+  } else {                                                                                       \
+    if (stream) hipLaunchKernelGGL((KERN<64, true>), grid, block, 0, s, p);                       \
+    else hipLaunchKernelGGL((KERN<64, false>), grid, block, 0, s, p);                             \
+  }
   switch (op) {
     case 0: ZL_LAUNCH(pack_qkv_kernel); break;
     case 1: ZL_LAUNCH(unpack_qkv_kernel); break;

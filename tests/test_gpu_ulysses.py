@@ -76,5 +76,11 @@ def test_ulysses_group8_many_heads():
     _run(G=8, H=160, hd=128, shard_lens=((38,), (37,), (38,), (37,), (38,), (37,), (38,), (37,)), seed=44)
 
 
+@pytest.mark.parametrize("hd", [64, 128])
+def test_ulysses_beyond_the_caches(hd):
+    # each of the four copies reads and writes more than 96 MiB: the non-temporal instances
+    _run(G=2, H=160 * 128 // hd, hd=hd, shard_lens=((1001, 700), (1000, 600)), seed=45)
+
+
 def test_ulysses_group1_is_identity_layout():
     _run(G=1, H=4, hd=128, shard_lens=((100, 7),), seed=43)
