@@ -727,8 +727,6 @@ __global__ __launch_bounds__(kDkdvThreads, 1) void bwd_fused_kernel(BwdParams p)
   if (threadIdx.x == 0 && p.wq_q) wq_finish2(p.wq_kv, p.wq_q);
 }
 
-}  // namespace
-
 template <int D>
 hipError_t launch_dkdv(BwdParams p, hipStream_t s) {
   const int grid = launch_grid(reinterpret_cast<const void*>(bwd_dkdv_kernel<D>), kDkdvThreads, p.n_kv_items, p.wq_kv);
@@ -762,6 +760,8 @@ template <int D>
 hipError_t launch_fused_d(const BwdParams& p, hipStream_t s) {
   return p.dq_first ? launch_fused<D, true>(p, s) : launch_fused<D, false>(p, s);
 }
+
+}  // namespace
 
 hipError_t launch_bwd_bf16(const BwdParams& p, int head_dim, int stage, hipStream_t s) {
   const dim3 block(NT);

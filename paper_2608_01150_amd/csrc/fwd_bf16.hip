@@ -436,8 +436,6 @@ __global__ __launch_bounds__(NT, PER_CU == 2 ? 4 : 1) void fwd_bf16_kernel(FwdPa
   if (tid == 0 && p.wq) wq_finish(p.wq);
 }
 
-}  // namespace
-
 template <int D, int PER_CU>
 hipError_t launch_per_cu(FwdParams p, hipStream_t s) {
   const int grid = launch_grid(reinterpret_cast<const void*>(fwd_bf16_kernel<D, PER_CU>), NT, p.n_items, p.wq);
@@ -453,6 +451,8 @@ hipError_t launch_d(const FwdParams& p, hipStream_t s) {
     if (p.many_long) return launch_per_cu<D, 2>(p, s);
   return launch_per_cu<D, 1>(p, s);
 }
+
+}  // namespace
 
 hipError_t launch_fwd_bf16(const FwdParams& p, int head_dim, hipStream_t s) {
   return head_dim == 128 ? launch_d<128>(p, s) : launch_d<64>(p, s);

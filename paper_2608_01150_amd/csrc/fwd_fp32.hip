@@ -231,8 +231,6 @@ __global__ __launch_bounds__(64 * NW, 2) void fwd_fp32_kernel(FwdParams p) {
   }
 }
 
-}  // namespace
-
 template <int D>
 hipError_t launch_d(const FwdParams& p, hipStream_t s) {
   // The grid's thread count has to stay below 2^32: further tiles are taken in turn.
@@ -241,6 +239,8 @@ hipError_t launch_d(const FwdParams& p, hipStream_t s) {
   hipLaunchKernelGGL(fwd_fp32_kernel<D>, grid, dim3(64 * NW), 0, s, p);
   return hipGetLastError();
 }
+
+}  // namespace
 
 hipError_t launch_fwd_fp32(const FwdParams& p, int head_dim, hipStream_t s) {
   return head_dim == 128 ? launch_d<128>(p, s) : launch_d<64>(p, s);

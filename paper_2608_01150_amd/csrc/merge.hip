@@ -115,8 +115,6 @@ __global__ __launch_bounds__(NT) void merge_kernel(MergeParams p) {
   if (sub == 0) p.lse[row] = lse;
 }
 
-}  // namespace
-
 // Partials per pass: 8 where one pass then holds every slot (fp32, 8 slots, 9,450
 // rows of 40 heads: 267 us, 4 per pass 268), and for more fp32 slots (16 slots:
 // 129.4 against 129.8).  Otherwise 4, whose fewer registers leave more waves in
@@ -135,6 +133,8 @@ void launch_merge_d(const MergeParams& p, bool part_bf16, dim3 grid, dim3 block,
   if (part_bf16) launch_merge_p<D, OUT_BF16, true>(p, grid, block, s);
   else launch_merge_p<D, OUT_BF16, false>(p, grid, block, s);
 }
+
+}  // namespace
 
 hipError_t launch_merge(const MergeParams& p, int head_dim, bool out_bf16, bool part_bf16, hipStream_t s) {
   const int upb = NT / (head_dim / (part_bf16 ? 8 : 4));  // units per block (see merge_kernel)
