@@ -349,6 +349,7 @@ struct Plan {
   std::vector<char> host;       // host copy (source of the upload)
   int32_t n_items = 0;          // forward items, or backward dK/dV items
   int32_t n_items2 = 0;         // backward dQ items
+  bool halves = false;          // forward or dQ items of halved query tiles (see halves_fit)
   bool many_long = false;       // forward: many_long_items
   bool fused = false;           // backward: dK/dV and dQ items in one launch,
   bool dq_first = false;        // the dQ items first
@@ -424,6 +425,7 @@ zl_status build_plan_host(const zl_seg_desc* d, int32_t H, zl_dtype dt, int op, 
     p.dq_first = b.dq_first;
     p.slots_offset = align256(kv.size() * sizeof(zl::Item));
     p.whole_bytes = p.slots_offset + qi.size() * sizeof(zl::Item);
+    p.halves = b.halves;
     if (b.halves) {
       qi = build_items(d, H, ZL_OP_BWD_DQ, {zl::kDqTileM / 2, zl::kDqTileN}, step);
       p.n_items2 = (int32_t)qi.size();
@@ -436,7 +438,8 @@ zl_status build_plan_host(const zl_seg_desc* d, int32_t H, zl_dtype dt, int op, 
     const int base_op = step ? ZL_OP_FWD : op;
     std::vector<zl::Item> items = build_items(d, H, base_op, tile_cfg(dt, base_op), step);
     if (items.size() > (size_t)INT32_MAX) return fail(ZL_ERR_UNSUPPORTED, "too many work items");
-    if (dt == ZL_BF16 && halves_fit(items, zl::kFwdTileM, 0))
+    p.halves = dt == ZL_BF16 && halves_fit(items, zl::kFwdTileM, 0);
+    if (p.halves)
       items = build_items(d, H, base_op, {zl::kFwdTileM / 2, zl::kFwdTileN}, step);
     p.n_items = (int32_t)items.size();
     p.many_long = many_long_items(items);
@@ -939,6 +942,18 @@ zl_status validate_bwd(const BwdCall& c, Shape* sh) {
 }
 
 
+// Whether dK/dV and dQ go out as one launch.  A dq that shares memory with q or dout
+// needs two: a dQ item reads only its own rows of them before it writes those of dq,
+// but dK/dV items read them all, and in one launch they would still be at it.
+bool one_launch(const Plan& plan, const BwdCall& c, const Shape& sh) {
+  const uintptr_t n = (uintptr_t)sh.total_q * c.H * c.hd * 2, dq = reinterpret_cast<uintptr_t>(c.dq);
+  for (const void* x : {c.q, c.dout}) {
+    const uintptr_t a = reinterpret_cast<uintptr_t>(x);
+    if (a < dq + n && dq < a + n) return false;
+  }
+  return plan.fused;
+}
+
 // Enqueues the backward kernels.  tables: the plan's dK/dV items, then (at
 // slots_offset bytes) its dQ items, on the device; workspace: bwd_workspace_bytes of device
 // memory.  No early return for Tq = 0: the ranges of a SHARD without query
@@ -981,7 +996,7 @@ zl_status launch_bwd(const BwdCall& c, const Shape& sh, const Plan& plan, const 
   const int hd = c.hd;
   hipError_t e = timed(ZL_K_BWD_PRE, s, [&] { return zl::launch_bwd_bf16(p, hd, 0, s); });
   // With profiling on the two kernels run apart, so that each is timed.
-  if (e == hipSuccess && plan.fused && !profiling())
+  if (e == hipSuccess && one_launch(plan, c, sh) && !profiling())
     return hip_status(zl::launch_bwd_bf16(p, hd, 3, s), "backward launch");
   if (e == hipSuccess) e = timed(ZL_K_BWD_DKDV, s, [&] { return zl::launch_bwd_bf16(p, hd, 1, s); });
   if (e == hipSuccess) e = timed(ZL_K_BWD_DQ, s, [&] { return zl::launch_bwd_bf16(p, hd, 2, s); });
@@ -1073,6 +1088,26 @@ zl_status zl_plan_dump(const zl_seg_desc* desc, int32_t H, int32_t hd, zl_dtype 
   if (tile_m) *tile_m = t.m;
   if (tile_n) *tile_n = t.n;
   return ok();
+}
+
+int32_t zl_launch_route(const zl_seg_desc* desc, int32_t H, int32_t hd, zl_dtype dt, int32_t op, const void* q,
+                        const void* dout, void* dq) {
+  Shape sh;
+  Plan plan;
+  if (op != ZL_OP_FWD && op != ZL_OP_BWD) return -1;
+  if (validate_common(H, hd, dt, 1.f, false) != ZL_OK || validate_desc(desc, 0, false, &sh) != ZL_OK ||
+      build_plan_host(desc, H, dt, op, plan) != ZL_OK)
+    return -1;
+  BwdCall c{};
+  c.H = H;
+  c.hd = hd;
+  c.q = q;
+  c.dout = dout;
+  c.dq = dq;
+  const bool one = op == ZL_OP_BWD && one_launch(plan, c, sh);
+  return (plan.halves ? zl::kRouteHalves : 0) | (one ? zl::kRouteOneLaunch : 0) |
+         (one && plan.dq_first ? zl::kRouteDqFirst : 0) |
+         (dt == ZL_BF16 && hd == 64 && plan.many_long ? zl::kRouteTwoPerCu : 0);
 }
 
 zl_status zl_profile_enable(int32_t on) {

@@ -152,6 +152,16 @@ zl_status stream_counters(hipStream_t s, int** out);
 // workgroups of the device).
 int launch_grid(const void* kernel, int block, int n_items, const int* ctr);
 
+// How a launch of a descriptor would be dispatched, as a sum of kRoute* (-1: invalid),
+// for the tests: which kernels a call reaches is a matter of its sizes.  op is ZL_OP_FWD or
+// ZL_OP_BWD; q, dout and dq are the addresses of a backward's tensors (never read).
+constexpr int kRouteHalves = 1;     // halved query tiles (forward, or dQ)
+constexpr int kRouteOneLaunch = 2;  // dK/dV and dQ in one launch,
+constexpr int kRouteDqFirst = 4;    // the dQ items first
+constexpr int kRouteTwoPerCu = 8;   // forward: two workgroups per compute unit
+extern "C" int32_t zl_launch_route(const zl_seg_desc* desc, int32_t num_heads, int32_t head_dim, zl_dtype dtype,
+                                   int32_t op, const void* q, const void* dout, void* dq);
+
 // Compute units of the current device (256, the MI355X's, where none is usable).
 int device_cus();
 
