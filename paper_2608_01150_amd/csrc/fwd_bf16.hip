@@ -143,7 +143,8 @@ __device__ __forceinline__ void fwd_store(const __attribute__((address_space(4))
 }
 
 // PER_CU: workgroups per compute unit that the registers leave room for (d = 64
-// with 128 VGPRs: two, and their LDS fits as well).
+// held to 128 VGPRs: two, and their LDS fits as well; three are spilled, reloaded at
+// an item's start and end).
 template <int D, int PER_CU>
 __global__ __launch_bounds__(NT, PER_CU == 2 ? 4 : 1) void fwd_bf16_kernel(FwdParams p) {
   constexpr int PITCH = Pad<D>::PITCH;

@@ -308,17 +308,18 @@ BwdPlan choose_bwd(const std::vector<zl::Item>& kv, const std::vector<zl::Item>&
 }
 
 // Whether a forward launch has the items for two workgroups per CU, where the
-// kernel's registers allow them (d = 64): at least four rounds of items with 1536
-// keys on average.  Two share a CU's matrix cores and hide each other's waits
-// (forward, 24 heads: 2 x 8,160 tokens 910 -> 839 us, 16 x 1560 339 -> 319 us), but
-// the last rounds of short items come out uneven (24 x 600 tokens 109 -> 129 us, 16
-// x 448 54 -> 73 us) and fewer items gain little (4,173 + 6 x 1,021 tokens, 984
-// items: 179 -> 181 us).
+// kernel's registers allow them (d = 64): at least four rounds, and 12,500 keys in
+// the items of a CU.  Two share a CU's matrix cores and hide each other's waits, but
+// the last rounds come out uneven, which shows where a CU has little to do.  Forward,
+// two per CU against one, by the keys per CU (rounds x keys of an item; 12 to 40
+// heads): 4,050 +17%; 5,500 to 6,200 +22, +4 and +9%; 7,200 to 9,000 -7 to +7%; 9,200 to
+// 10,300 -6 to +6%; 11,200 +4% (1700 tokens) and -1% (1560); 11,400 +4%; 12,300 +1% (2048
+// tokens) and -7% (1024); 12,600 to 13,800 -2 to -8%; beyond -7 to -11%.
 bool many_long_items(const std::vector<zl::Item>& items) {
   if (items.size() < (size_t)4 * zl::device_cus()) return false;
   int64_t keys = 0;
   for (const zl::Item& it : items) keys += it.k_len;
-  return keys >= (int64_t)items.size() * 1536;
+  return keys >= (int64_t)12500 * zl::device_cus();
 }
 
 struct MergeTable {

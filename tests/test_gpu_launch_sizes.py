@@ -3,11 +3,14 @@ their tiles against the fp64 oracle, and the same segment's results in both: a
 launch's size decides how its items are handed out (one round or queues, dK/dV
 and dQ in one launch or two, one or two workgroups per compute unit), never how
 an item is computed.  Bounds as in the other parity tests."""
+import numpy as np
 import pytest
 import torch
 
+import oracle
 from tests import _descs
-from tests._gpu import HAVE_GPU
+from tests._gpu import HAVE_GPU, api, to64
+from tests._route import TWO_PER_CU, route
 from tests.test_gpu_parity import run_and_compare
 
 pytestmark = [pytest.mark.gpu, pytest.mark.skipif(not HAVE_GPU, reason="needs a GPU")]
@@ -43,9 +46,6 @@ def test_one_long_segment(heads):
 
 def test_scores_jump_across_parts():
     """Keys that beat the running maximum far beyond the fast path's bound, each in another 32-key block."""
-    from tests._gpu import api, to64
-    import numpy as np
-    import oracle
     n, hd = 300, 128
     g = torch.Generator().manual_seed(81)
     q, k, v = (torch.randn((n, 1, hd), generator=g).to(torch.bfloat16) for _ in range(3))
@@ -60,7 +60,6 @@ def test_scores_jump_across_parts():
 
 def test_profiled_backward_has_the_same_bits():
     """With profiling on, dK/dV and dQ run as two launches: the same items, the same results."""
-    from tests._gpu import api
     d = _descs.mixed_small()
     H, hd = 40, 128
     desc = api.SegDesc.of(d)
@@ -93,30 +92,65 @@ def test_long_dq_items_first(hd):
 
 
 def test_two_workgroups_per_cu():
-    """d = 64 with more than four rounds of long items (1040 of 1601 keys): the forward runs two
-    workgroups per compute unit.  64 rows of every head against the oracle."""
-    from tests._gpu import api, to64
-    import numpy as np
-    import oracle
-    n, H, hd = 1601, 149, 64
+    """d = 64 with more than four rounds of long items: the forward runs two workgroups per compute unit.
+    Rows of every tile (the last one has 29) and head against the oracle, every row written."""
+    n, H, hd = 3101, 80, 64
     g = torch.Generator().manual_seed(83)
     q, k, v = (torch.randn((n, H, hd), generator=g).to(torch.bfloat16) for _ in range(3))
     d = _descs.desc(cu_q=(0, n), kind=(0,), kv_first=(0,), kv_count=(1,), cu_k=(0, n), block_index=(0,), num_slots=0)
-    out, lse, _, _ = api.attn_fwd(api.SegDesc.of(d), q.cuda(), k.cuda(), v.cuda(), hd ** -0.5)
-    rows = np.concatenate([np.arange(0, 48), np.arange(n - 16, n)])
-    out, lse = to64(out), to64(lse)
+    assert route(d, H, hd, api.ZL_OP_FWD) & TWO_PER_CU
+    out = torch.full((n, H, hd), float("nan"), dtype=torch.bfloat16, device="cuda")
+    lse = torch.full((n, H), float("nan"), device="cuda")
+    api.attn_fwd(api.SegDesc.of(d), q.cuda(), k.cuda(), v.cuda(), hd ** -0.5, out, lse)
+    assert torch.isfinite(out).all() and torch.isfinite(lse).all()
+    rows = np.array([r for t in range(0, n, 256) for r in (t, t + 31, t + 160, t + 255) if r < n] + [n - 1])
+    out, lse = to64(out[rows]), to64(lse[rows])
     for h in range(H):
         o, l = oracle.attend(q[rows, h].double().numpy(), k[:, h].double().numpy(), v[:, h].double().numpy(), hd ** -0.5)
-        assert np.abs(out[rows, h] - o).max() <= 2e-2
-        assert np.abs(lse[rows, h] - l).max() <= 1e-3
+        assert np.abs(out[:, h] - o).max() <= 2e-2
+        assert np.abs(lse[:, h] - l).max() <= 1e-3
+
+
+@pytest.mark.parametrize("part", [torch.float32, torch.bfloat16])
+def test_two_workgroups_per_cu_shard(part):
+    """The same launch with SHARD items (partials, and ring steps): 420 heads against 4 of them by themselves,
+    which run one workgroup per compute unit, bit for bit."""
+    nq, blocks, H, few, hd = 650, (2600, 2649), 420, 4, 64
+    g = torch.Generator(device="cuda").manual_seed(88)
+    q, k, v = (torch.randn((m, H, hd), generator=g, device="cuda").to(torch.bfloat16)
+               for m in (nq, sum(blocks), sum(blocks)))
+    d = _descs.desc(cu_q=(0, nq), kind=(1,), kv_first=(0,), kv_count=(2,), cu_k=(0, blocks[0], sum(blocks)),
+                    block_index=(1, 0), num_slots=2)
+    step = [_descs.desc(cu_q=(0, nq), kind=(1,), kv_first=(0,), kv_count=(1,), cu_k=(0, b), block_index=(0,), num_slots=1)
+            for b in blocks]
+    for x in (d, *step):
+        assert route(x, H, hd, api.ZL_OP_FWD) & TWO_PER_CU and not route(x, few, hd, api.ZL_OP_FWD) & TWO_PER_CU
+    res = []
+    for h in (H, few):
+        qh, kh, vh = (t[:, :h].contiguous() for t in (q, k, v))
+        _, _, o, l = api.attn_fwd(api.SegDesc.of(d), qh, kh, vh, hd ** -0.5, part_dtype=part)
+        out, lse = torch.empty_like(qh), torch.empty((nq, h), device="cuda")
+        acc = torch.empty((nq, h, hd), device="cuda"), torch.empty((nq, h), device="cuda")
+        row = 0
+        for i, b in enumerate(blocks):
+            api.attn_fwd_step(api.SegDesc.of(step[i]), qh, kh[row:row + b], vh[row:row + b], hd ** -0.5, out, lse, *acc,
+                              api.ZL_STEP_FIRST if i == 0 else api.ZL_STEP_LAST)
+            row += b
+        res.append((o, l, out, lse))
+    o, l, out, lse = res[0]
+    assert all(torch.isfinite(t).all() for t in res[0])
+    for a, b in zip((o[:, :, :few], l[:, :, :few], out[:, :few], lse[:, :few]), res[1]):
+        assert torch.equal(a, b)
+    for h in (0, few, H - 1):
+        ro, rl = oracle.attend(*(t[:, h].double().cpu().numpy() for t in (q, k, v)), hd ** -0.5)
+        assert np.abs(to64(out[:, h]) - ro).max() <= 2e-2 and np.abs(to64(lse[:, h]) - rl).max() <= 1e-3
 
 
 @pytest.mark.parametrize("hd", [64, 128])
-@pytest.mark.parametrize("n,others", [(448, 12), (300, 40), (1601, 14)])
+@pytest.mark.parametrize("n,others", [(448, 12), (300, 40), (1601, 24)])
 def test_bits_do_not_depend_on_the_launch(n, others, hd):
     """A segment alone (its items fit one round with compute units to spare) and among `others` more of
     its length (several rounds): the same outputs and gradients, bit for bit."""
-    from tests._gpu import api
     H, scale = 12, hd ** -0.5
     g = torch.Generator(device="cuda").manual_seed(84)
     q, k, v, do = (torch.randn((n * (1 + others), H, hd), generator=g, device="cuda").to(torch.bfloat16) for _ in range(4))
@@ -135,7 +169,6 @@ def test_bits_do_not_depend_on_the_launch(n, others, hd):
 @pytest.mark.parametrize("heads", [3, 40])
 def test_dq_in_place_of_q_or_dout(heads):
     """dq written over q or over dout: the gradients of the call with memory of its own, bit for bit."""
-    from tests._gpu import api
     n, hd = 1200, 128
     d = _descs.desc(cu_q=(0, n), kind=(0,), kv_first=(0,), kv_count=(1,), cu_k=(0, n), block_index=(0,), num_slots=0)
     desc = api.SegDesc.of(d)
