@@ -24,6 +24,20 @@ def test_tile_edges(lq, hd):
     run_and_compare(d, 3, hd, torch.float32, 900 + lq + hd, backward=False)
 
 
+def test_more_tiles_than_the_grid():
+    """A launch has at most 2^20 workgroups, further tiles are taken in turn: 33 one-token segments of 16,384
+    heads are 540,672 items of two tiles.  With one key, O is V's row and the LSE the scaled score."""
+    n, H, hd = 33, 16384, 64
+    g = torch.Generator(device="cuda").manual_seed(89)
+    q, k, v = (torch.randn((n, H, hd), generator=g, device="cuda") for _ in range(3))
+    cu = tuple(range(n + 1))
+    d = _descs.desc(cu_q=cu, kind=(0,) * n, kv_first=cu[:-1], kv_count=(1,) * n, cu_k=cu, block_index=(0,) * n, num_slots=0)
+    out, lse = torch.full_like(q, float("nan")), torch.full((n, H), float("nan"), device="cuda")
+    api.attn_fwd(api.SegDesc.of(d), q, k, v, 0.125, out, lse)
+    assert torch.equal(out, v)
+    assert (lse - 0.125 * (q.double() * k.double()).sum(-1)).abs().max().item() <= 1e-5
+
+
 @pytest.mark.parametrize("hd", [64, 128])
 def test_bits_do_not_depend_on_the_launch(hd):
     """A segment alone (30 tiles) and among 40 more of its length (1230 tiles): the same bits."""

@@ -10,7 +10,7 @@ import torch
 import oracle
 from tests import _descs
 from tests._gpu import HAVE_GPU, api, to64
-from tests._route import TWO_PER_CU, route
+from tests._route import DQ_FIRST, HALVES, ONE_LAUNCH, TWO_PER_CU, route
 from tests.test_gpu_parity import run_and_compare
 
 pytestmark = [pytest.mark.gpu, pytest.mark.skipif(not HAVE_GPU, reason="needs a GPU")]
@@ -33,6 +33,9 @@ def test_tile_edges(heads, hd):
     w = len(WHOLE)
     d = _descs.desc(cu_q=cu_q, kind=(0,) * w + (1,), kv_first=tuple(range(w + 1)), kv_count=(1,) * w + (len(blocks),),
                     cu_k=cu_k, block_index=(0,) * w + tuple(range(len(blocks))), num_slots=len(blocks))
+    # 1 head: halves throughout, one backward launch; 9: halves, dK/dV and dQ apart; 40: whole tiles in rounds
+    assert route(d, heads, hd, api.ZL_OP_FWD) == (HALVES if heads < 40 else 0)
+    assert route(d, heads, hd, api.ZL_OP_BWD) & (HALVES | ONE_LAUNCH) == {1: HALVES | ONE_LAUNCH, 9: HALVES, 40: ONE_LAUNCH}[heads]
     run_and_compare(d, heads, hd, torch.bfloat16, 60 + heads + hd)
 
 
@@ -58,10 +61,12 @@ def test_scores_jump_across_parts():
     assert np.abs(to64(lse) - ref["lse"]).max() <= 1e-3
 
 
-def test_profiled_backward_has_the_same_bits():
+@pytest.mark.parametrize("H", [3, 80])   # one round, and 1040 items in rounds
+def test_profiled_backward_has_the_same_bits(H):
     """With profiling on, dK/dV and dQ run as two launches: the same items, the same results."""
     d = _descs.mixed_small()
-    H, hd = 40, 128
+    hd = 128
+    assert route(d, H, hd, api.ZL_OP_BWD) & ONE_LAUNCH
     desc = api.SegDesc.of(d)
     g = torch.Generator().manual_seed(82)
     tq, tk = d["cu_seqlens_q"][-1], d["cu_seqlens_k"][-1]
@@ -88,7 +93,8 @@ def test_long_dq_items_first(hd):
     cu_k = (0, 130, 230, 360, 490, 520, 584)
     d = _descs.desc(cu_q=(0, 40, 104), kind=(1, 0), kv_first=(0, 5), kv_count=(5, 1), cu_k=cu_k,
                     block_index=(0, 1, 2, 3, 4, 0), num_slots=5)
-    run_and_compare(d, 100, hd, torch.bfloat16, 90 + hd)
+    assert route(d, 140, hd, api.ZL_OP_BWD) == ONE_LAUNCH | DQ_FIRST
+    run_and_compare(d, 140, hd, torch.bfloat16, 90 + hd)
 
 
 def test_two_workgroups_per_cu():
