@@ -225,6 +225,7 @@ KERNEL_SOURCES = {
     "fwd": ["fwd_bf16.hip"],
     "bwd_dkdv": ["bwd_bf16.hip"],
     "bwd_dq": ["bwd_bf16.hip"],
+    "bwd_fused": ["bwd_bf16.hip"],   # dK/dV and dQ in one launch
     "merge": ["merge.hip"],
 }
 COMMON_SOURCES = ["zl_device.h", "zl_internal.h"]

@@ -274,7 +274,7 @@ __device__ __forceinline__ float lanes_sum(float x) {
 // (grid G <= n) first runs position b, i.e. the first round of a
 // one-item-per-workgroup launch; afterwards it claims further positions of
 // its own XCD's queue with a device-scope atomic counter, and once that queue
-// is empty those of the next XCD's queue that holds any.  The XCDs of one GPU run
+// is empty positions of the next queue that still holds some.  The XCDs of one GPU run
 // at different speeds (several percent apart under load), and a fixed share
 // of the items per XCD leaves the fast ones idle while the slowest finishes;
 // here an XCD that runs ahead takes over the tail of the others' queues.

@@ -1096,6 +1096,7 @@ int32_t zl_launch_route(const zl_seg_desc* desc, int32_t H, int32_t hd, zl_dtype
   Shape sh;
   Plan plan;
   if (op != ZL_OP_FWD && op != ZL_OP_BWD) return -1;
+  std::lock_guard<std::mutex> lock(g_mu);
   if (validate_common(H, hd, dt, 1.f, false) != ZL_OK || validate_desc(desc, 0, false, &sh) != ZL_OK ||
       build_plan_host(desc, H, dt, op, plan) != ZL_OK)
     return -1;
