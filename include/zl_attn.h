@@ -275,9 +275,9 @@ zl_status zl_lse_merge_ex(const zl_seg_desc* desc, int32_t num_heads, int32_t he
  * rows, to which no query attends), rows of ranges no segment uses are not.
  * No atomics: results are deterministic, and a segment's do not depend on what
  * else the call holds (here and in every other entry point).  `flags` must be 0.
- * dq may be the
- * same memory as q or as dout (the call then takes two launches where it would
- * take one); no other output may share memory with an input.
+ * dq may be the same memory as q or as dout (the call then takes two launches
+ * where it would take one), and any gradient may lie in that of `out`, which is
+ * read before one is written; no other output may share memory with an input.
  * workspace: at least zl_workspace_size(..., ZL_OP_BWD) bytes of device
  * memory, 256-byte aligned, used by this call until it completes.
  */

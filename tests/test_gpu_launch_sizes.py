@@ -174,7 +174,8 @@ def test_bits_do_not_depend_on_the_launch(n, others, hd):
 
 @pytest.mark.parametrize("heads", [3, 40])
 def test_dq_in_place_of_q_or_dout(heads):
-    """dq written over q or over dout: the gradients of the call with memory of its own, bit for bit."""
+    """dq written over q or over dout, and each gradient over out: the gradients of the call with memory of its
+    own, bit for bit."""
     n, hd = 1200, 128
     d = _descs.desc(cu_q=(0, n), kind=(0,), kv_first=(0,), kv_count=(1,), cu_k=(0, n), block_index=(0,), num_slots=0)
     desc = api.SegDesc.of(d)
@@ -182,13 +183,11 @@ def test_dq_in_place_of_q_or_dout(heads):
     q, k, v, do = (torch.randn((n, heads, hd), generator=g, device="cuda").to(torch.bfloat16) for _ in range(4))
     out, lse, _, _ = api.attn_fwd(desc, q, k, v, hd ** -0.5)
     ref = api.attn_bwd(desc, q, k, v, out, lse, do, hd ** -0.5)
-    for name in ("q", "dout"):
-        for call in ("bwd", "noalloc"):
-            a, b = q.clone(), do.clone()
-            dq = a if name == "q" else b
-            if call == "bwd":
-                got = api.attn_bwd(desc, a, k, v, out, lse, b, hd ** -0.5, dq=dq)
-            else:
-                got = api.attn_bwd_noalloc(desc, a, k, v, out, lse, b, hd ** -0.5, dq, torch.empty_like(k), torch.empty_like(v))
-            for t, x, y in zip(("dq", "dk", "dv"), got, ref):
-                assert torch.equal(x, y), (name, call, t)
+    for grad, over in (("dq", "q"), ("dq", "dout"), ("dq", "out"), ("dk", "out"), ("dv", "out")):
+        for call in (api.attn_bwd, api.attn_bwd_noalloc):
+            t = {"q": q.clone(), "dout": do.clone(), "out": out.clone()}
+            to = {x: torch.empty_like(q) for x in ("dq", "dk", "dv")}
+            to[grad] = t[over]
+            got = call(desc, t["q"], k, v, t["out"], lse, t["dout"], hd ** -0.5, **to)
+            for name, x, y in zip(("dq", "dk", "dv"), got, ref):
+                assert torch.equal(x, y), (grad, over, call.__name__, name)
